@@ -24,6 +24,25 @@ __device__ __forceinline__ float dot(V3 a, V3 b) { return a.x * b.x + a.y * b.y 
 __device__ __forceinline__ V3 cross(V3 a, V3 b) {
   return {a.y * b.z - a.z * b.y, a.z * b.x - a.x * b.z, a.x * b.y - a.y * b.x};
 }
+// A sum of three products with the fused operations written out, the first
+// (y) or the second (x) product of the pair rounded on its own.  The compiler
+// may fuse either product of a plain sum, by the code around it; where the
+// result must not depend on that, one is named.
+__device__ __forceinline__ float dot_x(V3 a, V3 b) { return fmaf(a.z, b.z, fmaf(a.x, b.x, a.y * b.y)); }
+__device__ __forceinline__ float dot_y(V3 a, V3 b) { return fmaf(a.z, b.z, fmaf(a.y, b.y, a.x * b.x)); }
+__device__ __forceinline__ V3 cross_f(V3 a, V3 b) {
+  return {fmaf(a.y, b.z, -(a.z * b.y)), fmaf(a.z, b.x, -(a.x * b.z)), fmaf(a.x, b.y, -(a.y * b.x))};
+}
+// a + b with each sum rounded on its own (never fused with a product)
+__device__ __forceinline__ V3 add_f(V3 a, V3 b) {
+#pragma clang fp contract(off)
+  return {a.x + b.x, a.y + b.y, a.z + b.z};
+}
+__device__ __forceinline__ float sub_f(float a, float b) {
+#pragma clang fp contract(off)
+  return a - b;
+}
+__device__ __forceinline__ V3 fma3(float s, V3 a, V3 c) { return {fmaf(s, a.x, c.x), fmaf(s, a.y, c.y), fmaf(s, a.z, c.z)}; }
 __device__ __forceinline__ float maxabs(V3 a) { return fmaxf(fabsf(a.x), fmaxf(fabsf(a.y), fabsf(a.z))); }
 __device__ __forceinline__ V3 ld3(const float* p) { return {p[0], p[1], p[2]}; }
 
@@ -170,11 +189,27 @@ struct Stages {
   V3 B2, B4;  // field at the midpoint and the end (a map)
 };
 
-template <bool kMap, int NC>
+template <bool kMap, bool kNamed, int NC>
 __device__ __forceinline__ float rkn4_stages(const LegT<NC>& L, float h, V3 origin, const FieldDev& F, V3 B,
                                              Stages& S) {
   const float kl = kKappa * L.lam;
   const float h2 = 0.5f * h;
+  if constexpr (kNamed && !kMap) {  // (the fused operations written out, see leg_end)
+    const V3 c1 = cross_f(L.T, B);
+    S.k1 = kl * c1;
+    S.T2 = fma3(h2, S.k1, L.T);
+    const V3 c2 = cross_f(S.T2, B);
+    S.k2 = kl * c2;
+    S.T3 = fma3(h2, S.k2, L.T);
+    const V3 c3 = cross_f(S.T3, B);
+    S.k3 = kl * c3;
+    S.T4 = fma3(h, S.k3, L.T);
+    const V3 c4 = cross_f(S.T4, B);
+    S.k4 = kl * c4;
+    V3 e{fmaf(-kl, c2.x, S.k1.x), fmaf(-kl, c2.y, S.k1.y), fmaf(kl, c1.z, -S.k2.z)};
+    e = fma3(kl, c4, fma3(-kl, c3, e));
+    return h * h * maxabs(e);
+  }
   S.k1 = kl * cross(L.T, B);
   S.B2 = kMap ? field_at<true>(F, origin + L.r + h2 * L.T + (0.125f * h * h) * S.k1) : B;
   S.T2 = L.T + h2 * S.k1;
@@ -187,11 +222,34 @@ __device__ __forceinline__ float rkn4_stages(const LegT<NC>& L, float h, V3 orig
   return h * h * maxabs(S.k1 - S.k2 - S.k3 + S.k4);
 }
 
-template <bool kMap, int NC>
+template <bool kMap, bool kNamed, int NC>
 __device__ __forceinline__ void rkn4_advance(LegT<NC>& L, float h, V3 origin, const FieldDev& F, V3 B,
                                              const Stages& S) {
   const float kl = kKappa * L.lam;
   const float h2 = 0.5f * h, h6 = h * (1.0f / 6.0f), hh6 = h * h * (1.0f / 6.0f);
+  if constexpr (kNamed && !kMap) {  // (the same, with the fused operations written out)
+#pragma unroll
+    for (int j = 0; j < NC - 1; ++j) {
+      const V3 dT = L.dT[j];
+      const V3 d1 = kl * cross_f(dT, B);
+      const V3 c2 = cross_f(fma3(h2, d1, dT), B);
+      const V3 c3 = cross_f(fma3(h2, kl * c2, dT), B);
+      const V3 d3 = kl * c3;
+      const V3 c4 = cross_f(fma3(h, d3, dT), B);
+      L.dr[j] = fma3(hh6, fma3(kl, c3, fma3(kl, c2, d1)), fma3(h, dT, L.dr[j]));
+      L.dT[j] = fma3(h6, fma3(kl, c4, fma3(2.0f, fma3(kl, c2, d3), d1)), dT);
+    }
+    const V3 dT = L.dT[NC - 1];
+    const V3 d1 = fma3(kl, cross_f(dT, B), kKappa * cross_f(L.T, B));
+    const V3 d2 = fma3(kKappa, cross_f(S.T2, B), kl * cross_f(fma3(h2, d1, dT), B));
+    const V3 d3 = fma3(kKappa, cross_f(S.T3, B), kl * cross_f(fma3(h2, d2, dT), B));
+    const V3 d4 = fma3(kKappa, cross_f(S.T4, B), kl * cross_f(fma3(h, d3, dT), B));
+    L.dr[NC - 1] = fma3(hh6, add_f(add_f(d1, d2), d3), fma3(h, dT, L.dr[NC - 1]));
+    L.dT[NC - 1] = fma3(h6, add_f(fma3(2.0f, add_f(d2, d3), d1), d4), dT);
+    L.r = fma3(hh6, add_f(add_f(S.k1, S.k2), S.k3), fma3(h, L.T, L.r));
+    L.T = fma3(h6, add_f(fma3(2.0f, add_f(S.k2, S.k3), S.k1), S.k4), L.T);
+    return;
+  }
   if (!kMap) {
     // d(kappa*lambda*(T x B)) = kappa*lambda*(dT x B) + kappa*dlambda*(T x B)
 #pragma unroll
@@ -333,17 +391,59 @@ __device__ __forceinline__ float helix_distance(V3 r, V3 T, float lam, V3 B, V3 
   return s;
 }
 
+// The same with the fused operations written out (see leg_end).
+__device__ __forceinline__ float helix_distance_f(V3 r, V3 T, float lam, V3 B, V3 c, V3 n) {
+  const V3 k = (kKappa * lam) * cross_f(T, B);
+  float s;
+  {
+    const float a = 0.5f * dot_x(n, k), b = dot_y(n, T), c0 = dot_y(n, r - c);
+    if (fabsf(b) < 1e-9f) return __int_as_float(0x7fc00000);
+    s = fdiv_fast(-c0, b);
+    const float disc = fmaf(b, b, -((4.0f * a) * c0));
+    if (!(disc < 0.0f)) {
+      const float q = -0.5f * (b + copysignf(sqrtf(disc), b));
+      if (q != 0.0f) s = fdiv_fast(c0, q);
+    }
+  }
+  if (!isfinite(s)) return s;
+  const float bm = sqrtf(dot_x(B, B));
+  const V3 bhat = bm > 0.f ? (1.0f / bm) * B : V3{0.f, 0.f, 1.f};
+  const float om = kKappa * lam * bm;
+  const float inv_om = om != 0.f ? __builtin_amdgcn_rcpf(om) : 0.f;
+  const float tpar = dot_x(T, bhat);
+  const V3 tperp = fma3(-tpar, bhat, T), w = cross_f(T, bhat), along = tpar * bhat;
+#pragma unroll
+  for (int it = 0; it < 3; ++it) {
+    const float a = om * s;
+    float S, Cc, sh, ch;
+    sincosf(0.5f * a, &sh, &ch);
+    const float sa = 2.0f * sh * ch, vs = 2.0f * sh * sh, ca = sub_f(1.0f, vs);
+    if (fabsf(a) < 1e-3f) {
+      S = s * fmaf(-(a * a), 1.0f / 6.0f, 1.0f);
+      Cc = s * (0.5f * a) * fmaf(-(a * a), 1.0f / 12.0f, 1.0f);
+    } else {
+      S = sa * inv_om;
+      Cc = vs * inv_om;
+    }
+    const V3 p = fma3(Cc, w, fma3(S, tperp, fma3(tpar * s, bhat, r)));
+    const float fp = dot_x(n, fma3(sa, w, fma3(ca, tperp, along)));
+    if (fabsf(fp) < 1e-9f) return __int_as_float(0x7fc00000);
+    s = fmaf(-__builtin_amdgcn_rcpf(fp), dot_x(n, p - c), s);
+  }
+  return s;
+}
+
 struct LegStats {
   int trials, rejects;
 };
 
 // Adaptive RKN4 steps onto the plane (c, n) given relative to the origin.
-template <bool kMap, int NC>
+template <bool kMap, bool kNamed, int NC>
 __device__ bool land(LegT<NC>& L, V3 origin, V3 c, V3 n, const FieldDev& F, const CfgDev& cfg, float& h_trial,
                      float& path, LegStats& st) {
   for (int it = 0; it < cfg.max_rk; ++it) {
     const V3 B = field_at<kMap>(F, origin + L.r);
-    const float d = helix_distance(L.r, L.T, L.lam, B, c, n);
+    const float d = kNamed && !kMap ? helix_distance_f(L.r, L.T, L.lam, B, c, n) : helix_distance(L.r, L.T, L.lam, B, c, n);
     if (!isfinite(d)) return false;
     if (fabsf(d) < cfg.land_tol) {
       L.r = L.r + d * L.T;
@@ -354,14 +454,14 @@ __device__ bool land(LegT<NC>& L, V3 origin, V3 c, V3 n, const FieldDev& F, cons
     const bool limited = fabsf(d) < h_trial;
     const float h = copysignf(fminf(fabsf(d), h_trial), d);
     Stages S;
-    const float err = rkn4_stages<kMap>(L, h, origin, F, B, S);
+    const float err = rkn4_stages<kMap, kNamed>(L, h, origin, F, B, S);
     ++st.trials;
     if (!(err <= cfg.step_tol)) {
       ++st.rejects;
       h_trial = fabsf(h) * fmaxf(0.25f, 0.9f * sqrtf(sqrtf(fdiv_fast(cfg.step_tol, err))));
       continue;
     }
-    rkn4_advance<kMap>(L, h, origin, F, B, S);
+    rkn4_advance<kMap, kNamed>(L, h, origin, F, B, S);
     path += fabsf(h);
     const float grow = err > 0.0f ? fminf(4.0f, 0.9f * sqrtf(sqrtf(fdiv_fast(cfg.step_tol, err)))) : 4.0f;
     h_trial = limited ? fminf(cfg.step_max, fmaxf(h_trial, fabsf(h) * grow)) : fminf(cfg.step_max, fabsf(h) * grow);
@@ -369,16 +469,25 @@ __device__ bool land(LegT<NC>& L, V3 origin, V3 c, V3 n, const FieldDev& F, cons
   return false;
 }
 
-// Bound parameters on module A -> leg start (relative to A's centre).
-template <int NC>
-__device__ __forceinline__ void leg_start(const Module& A, const double* p, LegT<NC>& L, V3& uA, V3& vA) {
-  uA = ld3(A.u);
-  vA = ld3(A.v);
-  const float l0 = (float)p[0], l1 = (float)p[1];
+// Bound parameters on module A -> leg start (relative to A's centre).  The
+// sines and cosines of the angles come separately, so that a caller that
+// needs the start state twice keeps these and not the columns.
+struct LegAngles {
   float sp, cp, st, ct;
-  sincosf((float)p[2], &sp, &cp);
-  sincosf((float)p[3], &st, &ct);
-  L.r = l0 * uA + l1 * vA;
+};
+
+__device__ __forceinline__ LegAngles leg_angles(const double* p) {
+  LegAngles a;
+  sincosf((float)p[2], &a.sp, &a.cp);
+  sincosf((float)p[3], &a.st, &a.ct);
+  return a;
+}
+
+template <bool kNamed, int NC>
+__device__ __forceinline__ void leg_start(V3 uA, V3 vA, const double* p, const LegAngles& a, LegT<NC>& L) {
+  const float l0 = (float)p[0], l1 = (float)p[1];
+  const float sp = a.sp, cp = a.cp, st = a.st, ct = a.ct;
+  L.r = kNamed ? fma3(l0, uA, l1 * vA) : l0 * uA + l1 * vA;
   L.T = {cp * st, sp * st, ct};
   L.lam = (float)p[4];
 #pragma unroll
@@ -391,24 +500,34 @@ __device__ __forceinline__ void leg_start(const Module& A, const double* p, LegT
   L.dT[NC - 2] = {cp * ct, sp * ct, -st};
 }
 
+template <bool kNamed, int NC>
+__device__ __forceinline__ void leg_start(const Module& A, const double* p, LegT<NC>& L, V3& uA, V3& vA) {
+  uA = ld3(A.u);
+  vA = ld3(A.v);
+  leg_start<kNamed>(uA, vA, p, leg_angles(p), L);
+}
+
 // Landed free state -> bound parameters on module B and the bound-to-bound
 // Jacobian with the path-length correction.  dB = B's centre relative to
 // the leg origin; qop is the start's FP64 q/p (unchanged along the leg).
-template <int NC>
+// kNamed writes the fused operations of the sums of products out: the
+// search's results then do not depend on how the code around a leg is
+// arranged (in a plain sum the compiler may fuse either product).
+template <bool kNamed, int NC>
 __device__ __forceinline__ void leg_end(const LegT<NC>& L, V3 uA, V3 vA, const Module& Bm, V3 dB, V3 Bf, double qop,
                                         double* p, float J[5][5]) {
   const V3 uB = ld3(Bm.u), vB = ld3(Bm.v), nB = ld3(Bm.n);
   const V3 d = L.r - dB;
   const V3 T = L.T;
-  const float st2 = T.x * T.x + T.y * T.y;
+  const float st2 = kNamed ? fmaf(T.y, T.y, T.x * T.x) : T.x * T.x + T.y * T.y;
   const float st = sqrtf(st2);
-  p[0] = (double)dot(uB, d);
-  p[1] = (double)dot(vB, d);
+  p[0] = (double)(kNamed ? dot_y(uB, d) : dot(uB, d));
+  p[1] = (double)(kNamed ? dot_x(vB, d) : dot(vB, d));
   p[2] = (double)atan2_as(T.y, T.x);
   p[3] = (double)atan2_as(st, T.z);
   p[4] = qop;  // no energy loss: q/p keeps its FP64 value
-  const V3 kend = (kKappa * L.lam) * cross(T, Bf);
-  const float inT = fdiv_fast(1.0f, dot(nB, T));
+  const V3 kend = (kKappa * L.lam) * (kNamed ? cross_f(T, Bf) : cross(T, Bf));
+  const float inT = fdiv_fast(1.0f, kNamed ? dot_y(nB, T) : dot(nB, T));
   const float ist2 = fdiv_fast(1.0f, st2), ist = fdiv_fast(1.0f, st);
   V3 dr[5], dT[5];
   if (NC == 3) {
@@ -424,13 +543,23 @@ __device__ __forceinline__ void leg_end(const LegT<NC>& L, V3 uA, V3 vA, const M
   }
 #pragma unroll
   for (int j = 0; j < 5; ++j) {
-    const float ds = -dot(nB, dr[j]) * inT;
-    const V3 drc = dr[j] + ds * T;
-    const V3 dTc = dT[j] + ds * kend;
-    J[0][j] = dot(uB, drc);
-    J[1][j] = dot(vB, drc);
-    J[2][j] = (T.x * dTc.y - T.y * dTc.x) * ist2;
-    J[3][j] = -dTc.z * ist;
+    if (kNamed) {
+      const float ds = -(NC == 3 && j < 2 ? dot_x(nB, dr[j]) : dot_y(nB, dr[j])) * inT;
+      const V3 drc = fma3(ds, T, dr[j]);
+      const V3 dTc = fma3(ds, kend, dT[j]);
+      J[0][j] = dot_x(uB, drc);
+      J[1][j] = dot_x(vB, drc);
+      J[2][j] = fmaf(T.x, dTc.y, -(T.y * dTc.x)) * ist2;
+      J[3][j] = -dTc.z * ist;
+    } else {
+      const float ds = -dot(nB, dr[j]) * inT;
+      const V3 drc = dr[j] + ds * T;
+      const V3 dTc = dT[j] + ds * kend;
+      J[0][j] = dot(uB, drc);
+      J[1][j] = dot(vB, drc);
+      J[2][j] = (T.x * dTc.y - T.y * dTc.x) * ist2;
+      J[3][j] = -dTc.z * ist;
+    }
     J[4][j] = (j == 4) ? 1.0f : 0.0f;
   }
 }

@@ -188,14 +188,14 @@ __device__ bool fit_leg(const GeomDev& g, const FieldDev& F, const CfgDev& cfg, 
   load_module(g, dst, Bm);
   LegT<kMap ? 5 : 3> L;
   V3 uA, vA;
-  leg_start(Am, p, L, uA, vA);
+  leg_start<false>(Am, p, L, uA, vA);
   const V3 origin = ld3(Am.c);
   const V3 dB = ld3(Bm.c) - origin;
   float h = cfg.step_max, path = 0.f;
   LegStats st{0, 0};
-  if (!land<kMap>(L, origin, dB, ld3(Bm.n), F, cfg, h, path, st)) return false;
+  if (!land<kMap, false>(L, origin, dB, ld3(Bm.n), F, cfg, h, path, st)) return false;
   double pn[5];
-  leg_end(L, uA, vA, Bm, dB, field_at<kMap>(F, origin + L.r), p[4], pn, J);
+  leg_end<false>(L, uA, vA, Bm, dB, field_at<kMap>(F, origin + L.r), p[4], pn, J);
   bool good = true;
 #pragma unroll
   for (int k = 0; k < 5; ++k) good = good && isfinite(pn[k]);

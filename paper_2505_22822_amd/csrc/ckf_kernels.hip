@@ -196,6 +196,10 @@ __device__ __forceinline__ void store_rec(const Pool& P, int r, const Light& c, 
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x; }
 
+// The value as one that the compiler knows nothing about: expressions on
+// either side of it are not merged.
+__device__ __forceinline__ void opaque(float& x) { asm volatile("" : "+v"(x)); }
+
 __device__ __forceinline__ int wave_excl_scan(int v, int& total) {
   const int lane = lane_id();
   int x = v;
@@ -491,11 +495,11 @@ __device__ __forceinline__ void fin_append(const Workspace& w, int* status, int 
 }
 
 // C <- J C J^T on a pool record's covariance (J promoted to FP64), each new
-// element stored as soon as it is formed; the three the gate needs are
-// returned.  J's q/p row is the unit row (no energy loss along a leg), so
+// element stored as soon as it is formed; the three the gate needs and the
+// two the scattering changes are returned.  J's q/p row is the unit row (no energy loss along a leg), so
 // its products are the covariance's own q/p row and column.
 __device__ __forceinline__ void transport_cov_rec(const float J[5][5], const Pool& P, int r, double& c00, double& c01,
-                                                  double& c11) {
+                                                  double& c11, double& c22, double& c33) {
   double C[15];
   load_cov(P, r, C);
 #pragma unroll
@@ -517,6 +521,8 @@ __device__ __forceinline__ void transport_cov_rec(const float J[5][5], const Poo
       if (i == 0 && j == 0) c00 = s;
       if (i == 0 && j == 1) c01 = s;
       if (i == 1 && j == 1) c11 = s;
+        if (i == 2 && j == 2) c22 = s;
+        if (i == 3 && j == 3) c33 = s;
       PDr(P, r, PD_C + pk(i, j)) = s;
     }
   }
@@ -533,8 +539,7 @@ __global__ __launch_bounds__(kWave, kMinWaves) void k_ckf(CkfArgs A) {
   __shared__ int sh_seed[kMaxSlots], sh_event[kMaxSlots], sh_live[kMaxSlots], sh_step[kMaxSlots];
   __shared__ int sh_best_node[kMaxSlots], sh_best_nm[kMaxSlots], sh_best_holes[kMaxSlots];
   __shared__ double sh_best_chi2[kMaxSlots];
-  __shared__ int sh_n_out, sh_bcast;
-  __shared__ unsigned long long sh_node_base;
+  __shared__ int sh_n_out, sh_bcast, sh_full;  // sh_full: this wave's nodes exceeded the history's capacity
   __shared__ int sh_cnt[kCount ? CKF_CNT_N + 3 : 3][kWave];  // per-lane counters (kept out of registers)
 
   __shared__ LayerRec sh_layers[kMaxLayers];
@@ -596,6 +601,7 @@ __global__ __launch_bounds__(kWave, kMinWaves) void k_ckf(CkfArgs A) {
 
   sh_seed[lane] = -1;
   sh_live[lane] = 0;
+  if (lane == 0) sh_full = 0;
   __syncthreads();
 
   int cur = 0, n_in = 0;
@@ -605,7 +611,6 @@ __global__ __launch_bounds__(kWave, kMinWaves) void k_ckf(CkfArgs A) {
   // parts were found used up
   int part = blockIdx.x % kSeedQueues, parts_done = 0;
   for (;;) {
-    if (((volatile int*)A.status)[CKF_STATUS_FLAGS] & CKF_FLAG_NODE_CAPACITY) break;
     const Pool Pin = pool_at(base, cap, cur), Pout = pool_at(base, cap, 1 - cur);
 
     // ---- admission: fill free seed slots from the work queue
@@ -682,9 +687,6 @@ __global__ __launch_bounds__(kWave, kMinWaves) void k_ckf(CkfArgs A) {
     __syncthreads();
     for (int b0 = 0; b0 < n_in; b0 += kWave) {
       const int r = b0 + lane;
-      int slot = -1;
-      if (r < n_in) slot = PIr(Pin, r, PI_SLOT);
-      const bool act = slot >= 0;
       // outcome of this step: 0 nothing (dropped or idle), 1 the candidate
       // continues as it is, 2 it crossed a module (search), 3 it finished
       int outcome = 0;
@@ -699,26 +701,15 @@ __global__ __launch_bounds__(kWave, kMinWaves) void k_ckf(CkfArgs A) {
       // navigation state is written back into the candidate's own record.
       // Stage A: the next layer; then (learned form) the network for all
       // lanes together; stage B: module listing and the leg.
+      // The record's fields are requested in one round (a dead record's are
+      // read too and not used): the step has no load that waits for the slot.
       double p[5];
-      int surf = -1, nlist = 0, root = 0;
+      int slot = -1, surf = -1, nlist = 0, root = 0, nmh = 0;
       unsigned long long mask = 0;
       int list[kMaxList];
       float h = 0.f, path = 0.f;
-      Module Am;
-      LegT<kMap ? 5 : 3> L;
-      V3 uA, vA, origin, Pl, Tl;
-      bool go = false, need_list = false;
-      int lay = 0, excl = -1, nb_slot = -1, nb_row = -1;
-      Window win{0, 0, 0.f, 0.f};
-      float sb = 0.f;
-      long long t_nav = 0;
-      int prop[3] = {-1, -1, -1};
-      bool confident = false;
-      int pf_a = 0, pf_b = 0;  // the searched row's measurement range and largest var0 (loaded early)
-      float pf_mv = 0.f;
-      V3 kl{0.f, 0.f, 0.f};
-      auto stage_a = [&]() {
-        CNT_ADD(CKF_CNT_STEPS, 1);
+      if (r < n_in) {
+        slot = PIr(Pin, r, PI_SLOT);
 #pragma unroll
         for (int k = 0; k < 5; ++k) p[k] = PDr(Pin, r, (PD_P + k));
         surf = PIr(Pin, r, PI_SURF);
@@ -731,12 +722,38 @@ __global__ __launch_bounds__(kWave, kMinWaves) void k_ckf(CkfArgs A) {
         for (int k = 0; k < kMaxList; ++k) list[k] = PIr(Pin, r, (PI_LIST + k));
         h = PFr(Pin, r, PF_H);
         path = PFr(Pin, r, PF_PATH);
+        nmh = PIr(Pin, r, PI_NMH);
+      }
+      const bool act = slot >= 0;
+      Module Am;
+      LegT<kMap ? 5 : 3> L;
+      V3 uA, vA, origin, Pl, Tl;
+      V3 mn{0.f, 0.f, 0.f};  // normal and thickness of the module the candidate is on (for the scattering)
+      float mthick = 0.f;
+      LegAngles ang{0.f, 1.f, 0.f, 1.f};
+      bool go = false, need_list = false;
+      int lay = 0, excl = -1, nb_slot = -1, nb_row = -1;
+      Window win{0, 0, 0.f, 0.f};
+      float sb = 0.f;
+      long long t_nav = 0;
+      int prop[3] = {-1, -1, -1};
+      bool confident = false;
+      int pf_a = 0, pf_b = 0;  // the searched row's measurement range and largest var0 (loaded early)
+      float pf_mv = 0.f;
+      V3 kl{0.f, 0.f, 0.f};
+      auto stage_a = [&]() {
+        CNT_ADD(CKF_CNT_STEPS, 1);
         if (kCount) t_nav = clock64();
         // the start module and the leg's initial free state are the same for
         // the seed's listing, the next-layer search and the leg itself
         load_module(g, surf, Am);
-        leg_start(Am, p, L, uA, vA);
+        uA = ld3(Am.u);
+        vA = ld3(Am.v);
+        ang = leg_angles(p);
+        leg_start<true>(uA, vA, p, ang, L);
         origin = ld3(Am.c);
+        mn = ld3(Am.n);
+        mthick = Am.thick;
         if (root) mask |= 1ull << Am.layer;
         go = !root;
         // one listing call for both the seed's own layer and a newly found
@@ -893,9 +910,13 @@ __global__ __launch_bounds__(kWave, kMinWaves) void k_ckf(CkfArgs A) {
         if (act && want_geo) nlist = nl_geo;
         if (kCount && lane == 0) c_list_passes += passes;
       };
-      // stage B2: the leg to the next listed module.  The start state is
-      // rebuilt from the record rather than kept in registers across the
-      // network and the listing.
+      // stage B2: the leg to the next listed module.  The plain form keeps
+      // the module's axes and the angles' sines and cosines in registers
+      // across the listing; the learned form, whose network needs those
+      // registers, and the map form, whose five columns do, read them again.
+      // (Kept: the listing's round trips for the record and the module's
+      // record leave the step; plain kernel, 64 x mu = 200, with the record
+      // requested in one round: 8.85 -> 8.52 ms.)
       auto stage_b2 = [&]() {
         if (root) {  // the searched row (the seed's own module), loaded ahead of the search
           const int row = sh_event[slot] * g.n_surfaces + surf;
@@ -903,11 +924,24 @@ __global__ __launch_bounds__(kWave, kMinWaves) void k_ckf(CkfArgs A) {
           pf_b = A.m.offsets[row + 1];
           pf_mv = A.w.row_maxvar0[row];
         }
+        if (kLearned || kMap) {
 #pragma unroll
-        for (int k = 0; k < 5; ++k) p[k] = PDr(Pin, r, (PD_P + k));
-        load_module(g, surf, Am);
-        leg_start(Am, p, L, uA, vA);
-        origin = ld3(Am.c);
+          for (int k = 0; k < 5; ++k) p[k] = PDr(Pin, r, (PD_P + k));
+          load_module(g, surf, Am);
+          leg_start<true>(Am, p, L, uA, vA);
+          origin = ld3(Am.c);
+          mn = ld3(Am.n);
+          mthick = Am.thick;
+        } else {
+          // the state is built again from these values (a few products): its
+          // arithmetic stays apart from the navigation's, and its 20 columns
+          // are not held across the listing
+          opaque(ang.sp);
+          opaque(ang.cp);
+          opaque(ang.st);
+          opaque(ang.ct);
+          leg_start<true>(uA, vA, p, ang, L);
+        }
         if (need_list) {
           CNT_ADD(CKF_CNT_NAV_MODULES, nt);
           CNT_ADD(kNavOvf, ovf);
@@ -939,13 +973,13 @@ __global__ __launch_bounds__(kWave, kMinWaves) void k_ckf(CkfArgs A) {
             const V3 dB = ld3(Bm.c) - origin;
             LegStats ls{0, 0};
             CNT_ADD(CKF_CNT_LEGS, 1);
-            bool good = land<kMap>(L, origin, dB, ld3(Bm.n), A.f, cfg, h, path, ls);
+            bool good = land<kMap, true>(L, origin, dB, ld3(Bm.n), A.f, cfg, h, path, ls);
             CNT_ADD(CKF_CNT_RK_TRIALS, ls.trials);
             c_land = ls.trials + 1;
             CNT_ADD(CKF_CNT_RK_REJECTS, ls.rejects);
             if (good) {
               double pn[5];
-              leg_end(L, uA, vA, Bm, dB, field_at<kMap>(A.f, origin + L.r), p[4], pn, J);
+              leg_end<true>(L, uA, vA, Bm, dB, field_at<kMap>(A.f, origin + L.r), p[4], pn, J);
 #pragma unroll
               for (int k = 0; k < 5; ++k) good = good && isfinite(pn[k]);
 #pragma unroll
@@ -956,13 +990,17 @@ __global__ __launch_bounds__(kWave, kMinWaves) void k_ckf(CkfArgs A) {
             } else {
               moved = true;
               surf = m;
+              mn = ld3(Bm.n);
+              mthick = Bm.thick;
               outcome = (fabs(p[0]) <= (double)Bm.hw0 && fabs(p[1]) <= (double)Bm.hw1) ? 2 : 1;
             }
           }
         }
+        if (moved) {
 #pragma unroll
-        for (int k = 0; k < 5; ++k) PDr(Pin, r, (PD_P + k)) = p[k];
-        PIr(Pin, r, PI_SURF) = surf;
+          for (int k = 0; k < 5; ++k) PDr(Pin, r, (PD_P + k)) = p[k];
+          PIr(Pin, r, PI_SURF) = surf;
+        }
         PIr(Pin, r, PI_NLIST) = nlist;  // root flag cleared
         PIr(Pin, r, PI_MASK_LO) = (int)(unsigned)(mask & 0xffffffffull);
         PIr(Pin, r, PI_MASK_HI) = (int)(unsigned)(mask >> 32);
@@ -998,19 +1036,22 @@ __global__ __launch_bounds__(kWave, kMinWaves) void k_ckf(CkfArgs A) {
       // record, and the crossing lanes' exact loc0 windows
       int w_start = 0, w_n = 0, surf2 = -1;
       double g0 = 0.0, g1 = 0.0, k00 = 0.0, k01 = 0.0, k11 = 0.0;
+      double k22 = 0.0, k33 = 0.0;  // (the scattering's entries)
       if (outcome == 1 || outcome == 2) {
         if (moved) {
-          transport_cov_rec(J, Pin, r, k00, k01, k11);
+          transport_cov_rec(J, Pin, r, k00, k01, k11, k22, k33);
         } else {
           k00 = PDr(Pin, r, PD_C + 0);
           k01 = PDr(Pin, r, PD_C + 1);
           k11 = PDr(Pin, r, PD_C + 5);
+          k22 = PDr(Pin, r, PD_C + 9);
+          k33 = PDr(Pin, r, PD_C + 12);
         }
         if (outcome == 2) {
           CNT_ADD(CKF_CNT_CROSSED, 1);
-          g0 = PDr(Pin, r, PD_P + 0);
-          g1 = PDr(Pin, r, PD_P + 1);
-          surf2 = PIr(Pin, r, PI_SURF);
+          g0 = p[0];
+          g1 = p[1];
+          surf2 = surf;
           const int a = pf_a, b = pf_b;  // the row of surf2 (the seed's module, or the leg's target)
           if (b > a) {
             const double wd = sqrt(cfg.chi2_max * (k00 + (double)pf_mv));
@@ -1069,19 +1110,25 @@ __global__ __launch_bounds__(kWave, kMinWaves) void k_ckf(CkfArgs A) {
         n_acc = min(n_acc, cfg.branches);
         if (n_acc == 0) {  // a hole
           CNT_ADD(CKF_CNT_HOLES, 1);
-          const int nmh = PIr(Pin, r, PI_NMH) + (1 << 16);
+          nmh += 1 << 16;
           PIr(Pin, r, PI_NMH) = nmh;
-          if (cfg.material) {
-            double p[5], C[15];
-#pragma unroll
-            for (int k = 0; k < 5; ++k) p[k] = PDr(Pin, r, (PD_P + k));
-            load_cov(Pin, r, C);
+          if (cfg.material) {  // the scattering changes the two angle variances only
+            double C[15];
             Module M;
-            load_module_ms(g, surf2, M);
+            if (kMap) {  // (no registers left for them: read again)
+              C[pk(2, 2)] = PDr(Pin, r, PD_C + pk(2, 2));
+              C[pk(3, 3)] = PDr(Pin, r, PD_C + pk(3, 3));
+              load_module_ms(g, surf2, M);
+            } else {
+              C[pk(2, 2)] = k22;
+              C[pk(3, 3)] = k33;
+              M.n[0] = mn.x; M.n[1] = mn.y; M.n[2] = mn.z;
+              M.thick = mthick;
+            }
             apply_ms(M, cfg.mass, p, C);
             CNT_ADD(CKF_CNT_MS, 1);
-#pragma unroll
-            for (int k = 0; k < 15; ++k) PDr(Pin, r, (PD_C + k)) = C[k];
+            PDr(Pin, r, PD_C + pk(2, 2)) = C[pk(2, 2)];
+            PDr(Pin, r, PD_C + pk(3, 3)) = C[pk(3, 3)];
           }
           outcome = (nmh >> 16) > cfg.max_holes ? 3 : 1;
         }
@@ -1116,11 +1163,12 @@ __global__ __launch_bounds__(kWave, kMinWaves) void k_ckf(CkfArgs A) {
       int tot_nodes;
       const int noff = wave_excl_scan(n_kf, tot_nodes);
       __syncthreads();
-      if (lane == 0) {
-        sh_n_out += tot_out;
-        sh_node_base = tot_nodes > 0 ? atomicAdd(A.w.node_count, (unsigned long long)tot_nodes) : 0ull;
-      }
-      __syncthreads();
+      if (lane == 0) sh_n_out += tot_out;
+      // the pass's history nodes: the claim is only read (from lane 0) where
+      // the children are stored, so its round trip to memory runs beside the
+      // parents' loads
+      unsigned long long node_claim = 0;
+      if (lane == 0 && tot_nodes > 0) node_claim = atomicAdd(A.w.node_count, (unsigned long long)tot_nodes);
 
       // ---- phase 4: outputs, one output record per lane and round: the
       // parents' accepted measurements go through LDS, so a parent with
@@ -1149,9 +1197,6 @@ __global__ __launch_bounds__(kWave, kMinWaves) void k_ckf(CkfArgs A) {
 #pragma unroll
           for (int k = 0; k < (int)(kRecStride / 16); ++k) to[k] = from[k];
         } else {  // the Kalman-updated child for the parent's j-th accepted measurement
-          const long long nd = (long long)sh_node_base + sh_noff[src];
-          const bool room = nd + nkf <= A.w.node_cap;
-          if (!room && j == 0) atomicOr(A.status + CKF_STATUS_FLAGS, CKF_FLAG_NODE_CAPACITY);
           // the parent's module (from its search) and its normal and
           // thickness for the scattering, requested with the parent's state
           const int surf = sh_surf[src];
@@ -1166,6 +1211,15 @@ __global__ __launch_bounds__(kWave, kMinWaves) void k_ckf(CkfArgs A) {
           const float4 ms = A.w.m_sorted[i];
           kf_update(p, C, (double)ms.x, (double)ms.y, (double)ms.z, (double)ms.w, pc, Cc);
           CNT_ADD(CKF_CNT_KF, 1);
+          const long long nd =
+              (long long)(((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(node_claim >> 32), 0) << 32) |
+                          (unsigned)__builtin_amdgcn_readlane((int)(unsigned)node_claim, 0)) +
+              sh_noff[src];
+          const bool room = nd + nkf <= A.w.node_cap;
+          if (!room) {  // the history is full: the call fails and this wave stops after the step
+            sh_full = 1;
+            if (j == 0) atomicOr(A.status + CKF_STATUS_FLAGS, CKF_FLAG_NODE_CAPACITY);
+          }
           if (room) {
             Node* np = A.w.nodes + nd + j;
             np->parent = PIr(Pin, rs, PI_NODE);
@@ -1200,7 +1254,6 @@ __global__ __launch_bounds__(kWave, kMinWaves) void k_ckf(CkfArgs A) {
       if (cfg.all_tracks) {  // every finished candidate is kept (no per-seed best)
         if (outcome == 3) {
           CNT_ADD(CKF_CNT_FINISHED, 1);
-          const int nmh = PIr(Pin, r, PI_NMH);
           if ((nmh & 0xffff) >= cfg.min_meas)
             fin_append(A.w, A.status, sh_seed[slot], PIr(Pin, r, PI_NODE), nmh, PDr(Pin, r, PD_CHI2));
         }
@@ -1211,7 +1264,6 @@ __global__ __launch_bounds__(kWave, kMinWaves) void k_ckf(CkfArgs A) {
       double f_ch = 0.0;
       if (!cfg.all_tracks && outcome == 3) {
         CNT_ADD(CKF_CNT_FINISHED, 1);
-        const int nmh = PIr(Pin, r, PI_NMH);
         f_nm = nmh & 0xffff;
         f_ho = nmh >> 16;
         f_nd = PIr(Pin, r, PI_NODE);
@@ -1340,6 +1392,7 @@ __global__ __launch_bounds__(kWave, kMinWaves) void k_ckf(CkfArgs A) {
     }
     __syncthreads();
     if (kCount && lane == 0) CNT_ADD(CKF_CNT_CYC_STEP, (int)(clock64() - t_step));
+    if (sh_full) break;
     cur = 1 - cur;
     n_in = n_out_total;
   }
@@ -1613,17 +1666,17 @@ __global__ void __launch_bounds__(64) k_propagate_batch(GeomDev g, FieldDev F, C
   for (int k = 0; k < 15; ++k) C[k] = cov_in[15 * i + k];
   LegT<kMap ? 5 : 3> L;
   V3 uA, vA;
-  leg_start(Am, p, L, uA, vA);
+  leg_start<false>(Am, p, L, uA, vA);
   const V3 origin = ld3(Am.c);
   const V3 dB = ld3(Bm.c) - origin;
   float h = cfg.step_max, path = 0.f;
   LegStats st{0, 0};
-  const bool ok = land<kMap>(L, origin, dB, ld3(Bm.n), F, cfg, h, path, st);
+  const bool ok = land<kMap, false>(L, origin, dB, ld3(Bm.n), F, cfg, h, path, st);
   ok_out[i] = ok ? 1 : 0;
   if (!ok) return;
   double pn[5];
   float J[5][5];
-  leg_end(L, uA, vA, Bm, dB, field_at<kMap>(F, origin + L.r), p[4], pn, J);
+  leg_end<false>(L, uA, vA, Bm, dB, field_at<kMap>(F, origin + L.r), p[4], pn, J);
   transport_cov(J, C);
   for (int k = 0; k < 5; ++k) p_out[5 * i + k] = pn[k];
   for (int k = 0; k < 15; ++k) cov_out[15 * i + k] = C[k];
