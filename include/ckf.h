@@ -247,11 +247,11 @@ enum {
 /* Launch shape of ckf_find (chosen by the autotuner or the caller). */
 typedef struct ckf_launch {
   int32_t grid;              /* persistent workgroups; 0 = device default */
-  int32_t seeds_per_group;   /* concurrent seeds per 64-lane workgroup (1..64); 0 = default */
+  int32_t seeds_per_group;   /* concurrent seeds per 64-lane workgroup (1..64); 0 = default, by the batch's size */
   int32_t nodes_per_seed;    /* history capacity per seed in the workspace; 0 = default (32) */
   ckf_timer* timer;          /* NULL, or events recorded around the track-finding kernel */
-  int32_t waves_per_simd;    /* register budget of the kernel variant: 1, 2 or 3 waves per SIMD (0 = 3;
-                                a field map uses at most 2) */
+  int32_t waves_per_simd;    /* register budget of the kernel variant: 1, 2 or 3 waves per SIMD (0 =
+                                default; a field map uses at most 2) */
 } ckf_launch;
 
 /* Geometry: validates, builds the navigation grid on the host, uploads. */

@@ -374,18 +374,42 @@ int device_cus() {
   return cus;
 }
 
-constexpr int kDefaultSeedsPerGroup = 48;
+constexpr int kDefaultWaves = 2;          // the spill-free builds, the fastest on every batch measured
+constexpr int kDefaultSeedsPerGroup = 48;  // at most
+
+// Seeds per workgroup when the caller leaves it open, from the batch's seeds
+// per wave slot (x).  A step of a wave takes as long as its slowest lane, so
+// few seeds per wave make short steps, and a small batch is spread over the
+// chip: two slots' worth per wave up to 8 (half the slots in use: one wave per
+// SIMD steps faster than two), then x itself up to 16.  A large batch wants full lanes
+// but also some seeds left in the queue, so that uneven waves even out: three
+// quarters of x, up to 48.  k_ckf, ms (seeds per wave): 1,000 seeds 0.30 (1),
+// 0.38 (8), 0.59 (48); 5,000 seeds 0.47 (3), 0.41 (5), 0.75 (48); 10,000 seeds
+// 0.88 (2), 0.62 (8), 0.79 (16), 1.40 (48); 80,000 seeds 2.16 (8), 1.65 (24),
+// 1.69 (32), 1.94 (40), 2.23 (48); 640,000 seeds 9.4 (32), 8.5 (48), 8.8 (64).
+// Field map, 32,000 seeds: 1.30 (8), 0.87 (16), 0.94 (48); 128,000: 2.84 (16), 1.61 (48).
+int default_seeds_per_group(int n_seeds, int slots) {
+  const double x = (double)n_seeds / std::max(1, slots);
+  const double s = std::max({std::min(2.0 * x, 8.0), std::min(x, 16.0), 0.75 * x});
+  return std::max(1, std::min(kDefaultSeedsPerGroup, (int)std::ceil(s)));
+}
 constexpr int kNodesPerSeed = 32;
 constexpr int kFinPerSeed = 64;  // finished candidates kept per seed on average (tracks_per_seed = 0)
 
 ckf::Launch resolve_launch(const ckf_config* c, const ckf_launch* l, int n_seeds) {
   ckf::Launch r;
-  r.waves_per_simd = (l && l->waves_per_simd > 0) ? std::min(3, l->waves_per_simd) : 3;
-  r.seeds_per_group = (l && l->seeds_per_group > 0) ? std::min(64, l->seeds_per_group) : kDefaultSeedsPerGroup;
-  const int want = (n_seeds + r.seeds_per_group - 1) / r.seeds_per_group;
+  r.waves_per_simd = (l && l->waves_per_simd > 0) ? std::min(3, l->waves_per_simd) : kDefaultWaves;
   // one workgroup per wave slot: 4 SIMDs per CU times the waves per SIMD
-  const int dflt = device_cus() * 4 * r.waves_per_simd;
-  r.grid = std::max(1, std::min((l && l->grid > 0) ? l->grid : dflt, std::max(1, want)));
+  const int slots = (l && l->grid > 0) ? l->grid : device_cus() * 4 * r.waves_per_simd;
+  const bool open = !(l && l->seeds_per_group > 0);
+  r.seeds_per_group = open ? default_seeds_per_group(n_seeds, slots) : std::min(64, l->seeds_per_group);
+  const int want = (n_seeds + r.seeds_per_group - 1) / r.seeds_per_group;
+  r.grid = std::max(1, std::min(slots, std::max(1, want)));
+  // seeds the pools hold: at least grid * seeds_per_group (which is below
+  // n_seeds + seeds_per_group), and never less for more seeds, so that a
+  // workspace made for a batch serves every smaller one
+  r.pool_seeds = (long long)std::min<double>((double)n_seeds + 64,
+                                             (double)slots * (open ? kDefaultSeedsPerGroup : r.seeds_per_group));
   r.pool_cap = r.seeds_per_group * (c->max_live_per_seed * c->branches_per_surface + 1);
   r.nodes_per_seed = (l && l->nodes_per_seed > 0) ? l->nodes_per_seed : kNodesPerSeed;
   return r;
@@ -425,7 +449,7 @@ Layout layout(const ckf::Launch& L, int n_events, int n_surfaces, int n_seeds, l
   const size_t nb = (ns + 255) / 256 + 1;
   o.off_scan_a = take(nb * 4);
   o.off_scan_b = take(nb * 4);
-  o.off_pools = take((size_t)L.grid * 2 * L.pool_cap * ckf::kRecStride);
+  o.off_pools = take((size_t)L.pool_seeds * 2 * (L.pool_cap / L.seeds_per_group) * ckf::kRecStride);
   // every finished candidate (tracks_per_seed = 0 only)
   o.fin_cap = all_tracks ? (long long)ns * kFinPerSeed + 1024 : 0;
   const size_t fc = (size_t)std::max<long long>(o.fin_cap, 1), sn = all_tracks ? ns : 1;

@@ -171,6 +171,7 @@ struct Launch {
   int grid;
   int seeds_per_group;
   int pool_cap;
+  long long pool_seeds;  // seeds the workspace's pools are sized for
   int nodes_per_seed;
   int waves_per_simd;
 };

@@ -447,3 +447,29 @@ def test_all_finished_candidates_match_oracle_enumeration(ckf):
             na, nb = np.diff(got["offsets"])[a_], np.diff(got["offsets"])[b_]
             assert na > nb or (na == nb and (got["chi2"][a_] < got["chi2"][b_] or (
                 got["chi2"][a_] == got["chi2"][b_] and got["holes"][a_] <= got["holes"][b_])))
+
+
+@pytest.mark.parametrize("n", [1, 1023, 1025, 4097, 9000])
+def test_default_launch_shape_by_batch_size(ckf, n):
+    """The launch shape chosen from the number of seeds (one seed per wave up
+    to full waves) gives each seed the track of a fixed shape, in a workspace
+    that was sized for the whole event."""
+    import torch
+    from synth import barrel_endcap
+    det = barrel_endcap()
+    ev = make_event(det, 77, mu=200)
+    geo, fld = ckf.Geometry(det.as_arrays()), ckf.UniformField(0.0, 0.0, 2.0)
+    b = ckf.Batch.from_event(ev)
+    whole = ckf.Finder(geo, fld, b, counters=False)
+    pick = torch.arange(n, device="cuda")
+    part = ckf.Batch(b.n_events, b.n_surfaces, b.offsets, b.loc, b.var, b.seed_event[pick].contiguous(),
+                     b.seed_surface[pick].contiguous(), b.seed_params[pick].contiguous(), b.seed_cov[pick].contiguous())
+    f = ckf.Finder(geo, fld, part, counters=False)
+    assert f.workspace.numel() <= whole.workspace.numel()
+    f.workspace = whole.workspace
+    f.enqueue()
+    fixed = ckf.Finder(geo, fld, part, launch_cfg=ckf.launch(seeds_per_group=48, waves_per_simd=3), counters=False)
+    fixed.enqueue()
+    r, s = f.result(), fixed.result()
+    for k in ("n_tracks", "offsets", "meas", "params", "cov", "chi2", "seed"):
+        assert np.array_equal(r[k], s[k]), k
