@@ -180,3 +180,49 @@ def test_cluster_dense_modules(ckf, det_dense):
     np.testing.assert_array_equal(got["offsets"], ref["offsets"])
     np.testing.assert_array_equal(got["cell_cluster"], ref["label"])
     assert np.all(np.abs(got["loc"] - ref["loc"]) <= 4e-6)
+
+
+@pytest.mark.parametrize("sizes", [(1,), (255, 1, 300), (256, 256, 3), (257, 768, 769), (513, 1023, 1024),
+                                   (1025, 2, 1024, 5), (3, 2600), (2600,), (100,) * 40])
+def test_cluster_chunk_boundaries(ckf, det_dense, sizes):
+    """Modules whose cells end at, before and past the ends of the 256-cell
+    chunks and of the 1024 cells held on chip, with empty modules between
+    them and a last module that spans several chunks: every cell's cluster,
+    the offsets and the centroids are the oracle's."""
+    from oracle import clustering as OC
+    from synth.cells import Cells
+    S = det_dense.n_surfaces
+    n_grid, pitch = cell_grid(det_dense)
+    pix = [s for s in range(S) if n_grid[s, 0] >= 300 and n_grid[s, 1] >= 300]
+    rng = np.random.default_rng(sum(sizes) + len(sizes))
+    counts = np.zeros(S, np.int64)
+    c0, c1 = [], []
+    for k, n in enumerate(sizes):
+        counts[pix[3 * k]] = n  # (every third module holds cells)
+        at = np.sort(rng.choice(60 * 80, n, replace=False))
+        c0.append(at % 80 + 7)
+        c1.append(at // 80 + 11)
+    off = np.r_[0, np.cumsum(counts)].astype(np.int32)
+    m = int(off[-1])
+    cells = Cells(1, S, off, np.concatenate(c0).astype(np.int32), np.concatenate(c1).astype(np.int32),
+                  rng.uniform(0.2, 2.0, m).astype(np.float32), np.full(m, -1, np.int64))
+    ref = OC.cluster(cells, det_dense.as_arrays(), pitch)
+    _, got = _run(ckf, det_dense, cells)
+    assert got["status"] == 0
+    np.testing.assert_array_equal(got["offsets"], ref["offsets"])
+    np.testing.assert_array_equal(got["cell_cluster"], ref["label"])
+    assert np.all(np.abs(got["loc"] - ref["loc"]) <= 4e-6)
+
+
+def test_cluster_skips_a_row_out_of_order(ckf, det_dense):
+    """A row that is out of order is flagged and skipped; the rows around it
+    are clustered as if it were empty."""
+    from synth.cells import Cells
+    S = det_dense.n_surfaces
+    off = np.zeros(S + 1, np.int32)
+    off[6], off[7], off[8:] = 2, 1, 4  # row 5: cells 0, 1; row 6 runs backwards; row 7: cells 1 .. 3
+    cells = Cells(1, S, off, np.array([1, 2, 30, 31], np.int32), np.array([1, 1, 5, 5], np.int32),
+                  np.ones(4, np.float32), np.zeros(4, np.int64))
+    _, got = _run(ckf, det_dense, cells)
+    assert got["status"] & 1
+    np.testing.assert_array_equal(got["cell_cluster"], [0, 1, 2, 2])
