@@ -9,22 +9,28 @@
 // so a bad track whose key beats every bad track it shares a measurement
 // with is removed by the greedy too, at a point where its key is still the
 // same.  Each round therefore removes every such local maximum at once:
-//   shared  - shared counts of live tracks, bad flags and keys; the bad
-//             tracks clear the claim slots of their shared measurements;
+//   shared  - shared counts of the tracks that were bad (of all tracks, in
+//             round 0); the ones still bad form the round's list, with their
+//             keys, and clear the claim slots of their measurements;
 //   claim_a - each bad track puts its (share, chi2/ndf) key into the slots
-//             of its shared measurements (64-bit atomic max);
+//             of its measurements (64-bit atomic max; a measurement that it
+//             shares with no one has no other claim);
 //   claim_b - where a track's key equals the slot's, its index goes into
 //             the second slot (atomic max): ties go to the larger index;
-//   decide  - a bad track that holds both slots of all its shared
-//             measurements is marked for removal;
-//   apply   - marked tracks die and release their measurements.
+//   decide  - a bad track that holds both slots of all its measurements dies
+//             and releases them.
+// A bad track that is not removed only loses shared measurements, and a track
+// that is not bad never becomes it, so the lists shrink and a round costs what
+// its list holds.
+//
 // The rounds run on the device with no host synchronisation (the call can be
-// captured in a graph): a fixed number of rounds is launched, and once a
-// "shared" pass finds no bad track every later kernel returns at once.  The
-// bad-track count alternates between two words by round parity, so that a
-// round reads the previous round's count while its own is being formed.  A
-// last "shared" pass after the final round tells whether any bad track is
-// left.
+// captured in a graph).  Round 0, mostly the only large one, is one launch per
+// step.  The others, up to max_rounds, run in one kernel (k_res_tail), whose
+// workgroups wait for each other between the steps: one launch per step and
+// round cost 3 to 4 us each for 128 rounds by default that were, nearly all,
+// empty.  16 events, 194 000 tracks with a third duplicated: 2100 to 2600 us
+// -> 191 us, of which 130 are the 2.8M atomics of the counts and of round 0 (24
+// a nanosecond).
 #include "ckf_device.hpp"
 #include "ckf_kernels.hpp"
 
@@ -33,17 +39,49 @@ namespace ckf {
 namespace {
 
 constexpr int kResBlock = 256;
+constexpr int kResLanes = 8;   // lanes per track: tracks mostly hold 6 to 14 measurements
+constexpr int kTailBlock = 1024;
+constexpr int kTailTracks = kTailBlock / kResLanes;
+constexpr int kTailGrid = 256;     // workgroups of k_res_tail
+constexpr int kTailBuffer = 1024;  // of a list's tracks in a workgroup
+constexpr int kTailAlone = 256;    // bad tracks from which on one workgroup goes on by itself
+constexpr int kTailLines = 8;      // copies of the words that all wait for or report to, a line each
+constexpr int kLine = 32;          // words
+constexpr int kResWords = (1 + 2 * kTailLines) * kLine;  // counters, and the two kinds of lines
 
 struct ResWs {
   int* use;                  // [n_meas] live tracks holding the measurement
   unsigned long long* slot_a;  // [n_meas]
   int* slot_b;               // [n_meas]
-  unsigned long long* key;   // [cap_tracks]
-  int* state;                // [cap_tracks] 1 live, 0 removed, -1 invalid; 2 marked this round (transient)
-  int* bad;                  // [cap_tracks] 1 if bad this round
-  int* n_bad;                // [2] bad tracks of the rounds of even / odd index
+  unsigned long long* key;   // [cap_tracks] of a bad track (in round 0: 0 of any other; a bad one's is not 0)
+  int* state;                // [cap_tracks] 1 live, 0 removed, -1 invalid
+  int* list[2];              // [cap_tracks] bad tracks of the rounds of even / odd index from round 1
+  int* n_list;               // [4] their number: round 0 (1 if any), round 1, even rounds, odd rounds
   int* rounds;               // [1] rounds that removed tracks
+  int* converged;            // [1]
+  int *joined;               // [1] k_res_tail: workgroups that run,
+  int *command, *done;       // [kTailLines lines] the step they work on and the times that one was done with its step
 };
+
+struct ResTracks {
+  const int* n_tracks;
+  int cap_tracks;
+  const int *off, *meas;
+  const double* chi2;
+  const int* ndf;
+  int max_shared;
+};
+
+// Everything that passes between workgroups of one kernel (kShared) is read and
+// written past the caches that they don't share.
+template <bool kShared = true, class T>
+__device__ __forceinline__ T peek(const T* p) {
+  return kShared ? __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *p;
+}
+template <class T>
+__device__ __forceinline__ void poke(T* p, T v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 
 __device__ __forceinline__ bool track_range(const int* off, int t, long long cap_meas, long long& a, long long& b) {
   a = off[t];
@@ -51,32 +89,59 @@ __device__ __forceinline__ bool track_range(const int* off, int t, long long cap
   return a >= 0 && b <= cap_meas && a <= b;
 }
 
+// Waits until this wave's writes are where every workgroup sees them.  All that
+// workgroups pass to each other in one kernel goes by agent-scope atomics, past
+// the L2s that are not shared, so no write-back or invalidation of those is
+// needed (with the ones of a __threadfence, 128 rounds over 600 tracks took 7.1
+// ms instead of 2.0).
+__device__ __forceinline__ void settle() {
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+  __builtin_amdgcn_s_waitcnt(0);
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+}
+
+__device__ __forceinline__ int* bad_count(const ResWs& w, int r) { return w.n_list + (r < 2 ? r : 2 + (r & 1)); }
+
+// `v` of the lanes of this lane's track, as the low bits of the result
+__device__ __forceinline__ unsigned track_ballot(bool v) {
+  return (unsigned)(__ballot(v) >> (threadIdx.x & 63 & ~(kResLanes - 1))) & ((1u << kResLanes) - 1);
+}
+
 __global__ void k_res_init(long long n_meas, int cap_tracks, ResWs w) {
   const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n_meas) w.use[i] = 0;
-  if (i < cap_tracks) {
-    w.state[i] = 0;
-    w.bad[i] = 0;
+  if (i < n_meas) {
+    w.use[i] = 0;
+    w.slot_a[i] = 0ull;
+    w.slot_b[i] = -1;
   }
+  if (i < cap_tracks) w.state[i] = 0;
   if (i == 0) {
-    w.n_bad[0] = w.n_bad[1] = 0;
-    *w.rounds = 0;
+    w.n_list[0] = w.n_list[1] = w.n_list[2] = w.n_list[3] = 0;
+    *w.rounds = *w.converged = 0;
+    *w.joined = 0;
+    for (int k = 0; k < kTailLines; ++k) w.command[k * kLine] = w.done[k * kLine] = 0;
   }
 }
 
 // every live track's measurements counted; tracks with ids out of range
 // are invalid and take no part
-__global__ void k_res_count(const int* __restrict__ n_tracks_p, int cap_tracks, long long cap_meas,
-                            const int* __restrict__ off, const int* __restrict__ meas, long long n_meas, ResWs w) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  const int n_t = min(*n_tracks_p, cap_tracks);
-  if (t >= n_t) return;
-  long long a, b;
-  bool ok = track_range(off, t, cap_meas, a, b);
-  for (long long k = a; ok && k < b; ++k) ok = meas[k] >= 0 && meas[k] < n_meas;
-  w.state[t] = ok ? 1 : -1;
+__global__ void __launch_bounds__(kResBlock) k_res_count(ResTracks q, long long cap_meas, long long n_meas, ResWs w) {
+  const long long g = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  const int l = threadIdx.x & (kResLanes - 1);
+  const int n_t = min(*q.n_tracks, q.cap_tracks);
+  const bool on = g / kResLanes < n_t;
+  const int t = on ? (int)(g / kResLanes) : 0;
+  long long a = 0, b = 0;
+  bool ok = on && track_range(q.off, t, cap_meas, a, b);
+  const int m = ok && a + l < b ? q.meas[a + l] : 0;
+  ok = ok && m >= 0 && m < n_meas;
+  for (long long k = a + l + kResLanes; ok && k < b; k += kResLanes) ok = q.meas[k] >= 0 && q.meas[k] < n_meas;
+  ok = track_ballot(!ok) == 0;
+  if (!on) return;
+  if (l == 0) w.state[t] = ok ? 1 : -1;
   if (!ok) return;
-  for (long long k = a; k < b; ++k) atomicAdd(&w.use[meas[k]], 1);
+  if (a + l < b) atomicAdd(&w.use[m], 1);
+  for (long long k = a + l + kResLanes; k < b; k += kResLanes) atomicAdd(&w.use[q.meas[k]], 1);
 }
 
 __device__ __forceinline__ unsigned long long share_key(int s, int n, double chi2, int ndf) {
@@ -88,91 +153,277 @@ __device__ __forceinline__ unsigned long long share_key(int s, int n, double chi
   return (r << 31) | (unsigned long long)(__float_as_uint(q) & 0x7fffffffu);
 }
 
-__global__ void k_res_shared(const int* __restrict__ n_tracks_p, int cap_tracks, const int* __restrict__ off,
-                             const int* __restrict__ meas, const double* __restrict__ chi2,
-                             const int* __restrict__ ndf, int max_shared, ResWs w, int r) {
-  if (r > 0 && w.n_bad[(r - 1) & 1] == 0) return;  // converged in an earlier round
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  const int n_t = min(*n_tracks_p, cap_tracks);
-  if (t >= n_t) return;
-  w.bad[t] = 0;
-  if (w.state[t] != 1) return;
-  const long long a = off[t], b = off[t + 1];
+// The steps of a round, for a track; by all its lanes together (shared_by: by
+// all lanes of the wave).  kTail: in k_res_tail.
+
+// the track's shared measurements, if it lives
+template <bool kTail>
+__device__ __forceinline__ int shared_by(const ResTracks& q, const ResWs& w, int t, bool on, int& a, int& b) {
+  const int l = threadIdx.x & (kResLanes - 1);
+  on = on && peek<kTail>(&w.state[t]) == 1;
+  a = on ? q.off[t] : 0;
+  b = on ? q.off[t + 1] : 0;
   int s = 0;
-  for (long long k = a; k < b; ++k) s += w.use[meas[k]] > 1 ? 1 : 0;
-  if (s <= max_shared) return;
-  w.bad[t] = 1;
-  w.key[t] = share_key(s, (int)(b - a), chi2[t], ndf[t]);
-  atomicAdd(&w.n_bad[r & 1], 1);
-  for (long long k = a; k < b; ++k) {
-    const int m = meas[k];
-    if (w.use[m] > 1) {
-      w.slot_a[m] = 0ull;
-      w.slot_b[m] = -1;
+  for (int k = a + l; __any(k < b); k += kResLanes)
+    s += __popc(track_ballot(k < b && peek<kTail>(&w.use[q.meas[k]]) > 1));
+  return s;
+}
+
+// A workgroup's part of a list on its way out: one add to the list's counter
+// per flush.  (One per wave took 35 ns each, 25 000 of them 850 us.)
+struct ResBuffer {
+  int n, at;
+  int track[kTailBuffer];
+};
+
+__device__ __forceinline__ void res_flush(const ResWs& w, int r, ResBuffer& buf) {
+  __syncthreads();
+  const int n = buf.n;
+  if (threadIdx.x == 0 && n) buf.at = atomicAdd(bad_count(w, r), n);
+  __syncthreads();
+  for (int i = threadIdx.x; i < n; i += kTailBlock) poke(&w.list[r & 1][buf.at + i], buf.track[i]);
+  __syncthreads();
+  if (threadIdx.x == 0) buf.n = 0;
+  __syncthreads();
+}
+
+// on the list of round r >= 1, its slots cleared, if it is still bad
+template <bool kTail>
+__device__ __forceinline__ void list_bad(const ResTracks& q, const ResWs& w, ResBuffer& buf, int t, bool on) {
+  const int l = threadIdx.x & (kResLanes - 1);
+  int a, b;
+  const int s = shared_by<kTail>(q, w, t, on, a, b);
+  if (!(a < b && s > q.max_shared)) return;
+  if (l == 0) {
+    buf.track[atomicAdd(&buf.n, 1)] = t;
+    poke(&w.key[t], share_key(s, b - a, q.chi2[t], q.ndf[t]));
+  }
+  for (int k = a + l; k < b; k += kResLanes) {
+    const int m = q.meas[k];
+    poke(&w.slot_a[m], 0ull);
+    poke(&w.slot_b[m], -1);
+  }
+}
+
+// f(i, i < n) for the workgroup's share of 0 .. n - 1, a track's lanes an
+// index; the tracks that f lists leave through buf.
+template <class F>
+__device__ __forceinline__ void res_list(const ResWs& w, int r, ResBuffer& buf, int n, int block, int blocks, F f) {
+  if (threadIdx.x == 0) buf.n = 0;
+  __syncthreads();
+  int room = kTailBuffer;
+  for (long long i0 = (long long)block * kTailTracks; i0 < n; i0 += (long long)blocks * kTailTracks) {
+    if (room < kTailTracks) {
+      res_flush(w, r, buf);
+      room = kTailBuffer;
+    }
+    const int i = (int)i0 + (int)threadIdx.x / kResLanes;
+    f(i, i < n);
+    room -= kTailTracks;
+  }
+  res_flush(w, r, buf);
+}
+
+__device__ __forceinline__ void claim_a(const ResTracks& q, const ResWs& w, int t, unsigned long long key) {
+  const int b = q.off[t + 1];
+  for (int k = q.off[t] + (threadIdx.x & (kResLanes - 1)); k < b; k += kResLanes)
+    atomicMax(&w.slot_a[q.meas[k]], key);
+}
+
+template <bool kTail>
+__device__ __forceinline__ void claim_b(const ResTracks& q, const ResWs& w, int t, unsigned long long key) {
+  const int b = q.off[t + 1];
+  for (int k = q.off[t] + (threadIdx.x & (kResLanes - 1)); k < b; k += kResLanes) {
+    const int m = q.meas[k];
+    if (peek<kTail>(&w.slot_a[m]) == key) atomicMax(&w.slot_b[m], t);
+  }
+}
+
+template <bool kTail>
+__device__ __forceinline__ void decide(const ResTracks& q, const ResWs& w, int t, unsigned long long key) {
+  const int l = threadIdx.x & (kResLanes - 1);
+  const int a = q.off[t], b = q.off[t + 1];
+  bool top = true;
+  for (int k = a + l; top && k < b; k += kResLanes) {
+    const int m = q.meas[k];
+    top = peek<kTail>(&w.slot_b[m]) == t && peek<kTail>(&w.slot_a[m]) == key;
+  }
+  if (track_ballot(!top)) return;
+  if (l == 0) poke(&w.state[t], 0);
+  for (int k = a + l; k < b; k += kResLanes) atomicSub(&w.use[q.meas[k]], 1);
+}
+
+// step 1, 2: the claims; 3: decide
+template <int kStep, bool kTail>
+__device__ __forceinline__ void res_track(const ResTracks& q, const ResWs& w, int t, unsigned long long key) {
+  if (kStep == 1)
+    claim_a(q, w, t, key);
+  else if (kStep == 2)
+    claim_b<kTail>(q, w, t, key);
+  else
+    decide<kTail>(q, w, t, key);
+}
+
+// Round 0, over all tracks: shared (the slots are cleared already, and no list
+// is made: its counter would see every wave).
+__global__ void __launch_bounds__(kResBlock) k_res_shared(ResTracks q, ResWs w) {
+  const long long g = (long long)blockIdx.x * kResBlock + threadIdx.x;
+  const bool on = g / kResLanes < min(*q.n_tracks, q.cap_tracks);
+  const int t = on ? (int)(g / kResLanes) : 0;
+  int a, b;
+  const int s = shared_by<false>(q, w, t, on, a, b);
+  const bool bad = a < b && s > q.max_shared;
+  if (on && g % kResLanes == 0) w.key[t] = bad ? share_key(s, b - a, q.chi2[t], q.ndf[t]) : 0ull;
+  if (__any(bad) && (threadIdx.x & 63) == 0) *bad_count(w, 0) = 1;  // (the same value from every wave)
+}
+
+template <int kStep>
+__global__ void __launch_bounds__(kResBlock) k_res_step(ResTracks q, ResWs w) {
+  if (*bad_count(w, 0) == 0) return;
+  const long long g = (long long)blockIdx.x * kResBlock + threadIdx.x;
+  if (g / kResLanes >= min(*q.n_tracks, q.cap_tracks)) return;
+  const int t = (int)(g / kResLanes);
+  const unsigned long long key = w.key[t];
+  if (key) res_track<kStep, false>(q, w, t, key);
+}
+
+// Round 1's list: the tracks that round 0 left bad.
+__global__ void __launch_bounds__(kTailBlock) k_res_left(ResTracks q, ResWs w) {
+  __shared__ ResBuffer buf;
+  if (*bad_count(w, 0) == 0) return;
+  res_list(w, 1, buf, min(*q.n_tracks, q.cap_tracks), blockIdx.x, gridDim.x,
+           [&](int i, bool on) { list_bad<false>(q, w, buf, on ? i : 0, on && w.key[i] != 0); });
+}
+
+// A step of round r >= 1 for workgroup `block` of `blocks`; step 0: shared,
+// from the list of round r - 1.
+__device__ __forceinline__ void res_step(const ResTracks& q, const ResWs& w, ResBuffer& buf, int r, int step, int block,
+                                         int blocks) {
+  const int from = step == 0 ? r - 1 : r;
+  const int n = peek(bad_count(w, from));
+  const int* list = w.list[from & 1];
+  if (step == 0) {
+    res_list(w, r, buf, n, block, blocks,
+             [&](int i, bool on) { list_bad<true>(q, w, buf, on ? peek(&list[i]) : 0, on); });
+    return;
+  }
+  for (long long i = (long long)block * kTailTracks + threadIdx.x / kResLanes; i < n;
+       i += (long long)blocks * kTailTracks) {
+    const int t = peek(&list[i]);
+    const unsigned long long key = peek(&w.key[t]);
+    if (step == 1)
+      res_track<1, true>(q, w, t, key);
+    else if (step == 2)
+      res_track<2, true>(q, w, t, key);
+    else
+      res_track<3, true>(q, w, t, key);
+  }
+}
+
+// Workgroups that a list of n tracks is worth.
+__device__ __forceinline__ int res_need(int n) {
+  return n <= kTailAlone ? 1 : min(kTailGrid, (n + kTailTracks - 1) / kTailTracks);
+}
+
+// Rounds 1 to max_rounds, from the list of round 1.  Workgroups wait only for
+// workgroups that run: each joins when it starts, the first to join leads, and
+// the leader gives out a step (command: its number, and how many of those that
+// have joined by then take part) once all that took part in the last one are
+// done with it.  One that joins later takes part from the next step.  No wait
+// needs a workgroup that is not on the chip.  The lists only shrink: a
+// workgroup that they no longer need leaves, and the leader ends alone, without
+// commands (-1 ends the others).
+//
+// Bound by the latency of reads past the caches, three or four in a row per
+// step.  With a launch per step and round instead, 128 rounds: 600 tracks in
+// one chain 3.7 -> 2.0 ms a call, 200 000 15.6 -> 11.1 ms; 40 000 tracks of
+// random neighbours (57 rounds) 3.4 -> 1.4 ms.
+__global__ void __launch_bounds__(kTailBlock) k_res_tail(ResTracks q, ResWs w, int max_rounds) {
+  __shared__ int sh;
+  __shared__ ResBuffer buf;
+  const int t = threadIdx.x;
+  // (these two counts stay as they are in this kernel)
+  const int n0 = *bad_count(w, 0), n1 = *bad_count(w, 1);
+  if (n0 == 0 || n1 == 0 || max_rounds == 1) {  // no further round: no step is given out
+    if (blockIdx.x == 0 && t == 0) {
+      *w.rounds = n0 ? 1 : 0;
+      *w.converged = n0 == 0 || n1 == 0;
+    }
+    return;
+  }
+  if (t == 0) sh = atomicAdd(w.joined, 1);
+  __syncthreads();
+  const int me = sh;
+  __syncthreads();
+  int need = res_need(n1);
+  if (me >= need) return;
+  if (me > 0) {
+    int* const command = w.command + me % kTailLines * kLine;
+    for (int last = 0;;) {
+      if (t == 0) {
+        while ((sh = peek(command)) == last) __builtin_amdgcn_s_sleep(1);
+        settle();
+      }
+      __syncthreads();
+      const int c = sh, team = c & 511;
+      if (c < 0 || me >= (c >> 9 & 511)) return;
+      last = c;
+      if (me < team) {
+        res_step(q, w, buf, c >> 20, c >> 18 & 3, me, team);
+        settle();
+      }
+      __syncthreads();
+      if (me < team && t == 0) atomicAdd(w.done + me % kTailLines * kLine, 1);
     }
   }
-}
-
-__global__ void k_res_claim_a(const int* __restrict__ n_tracks_p, int cap_tracks, const int* __restrict__ off,
-                              const int* __restrict__ meas, ResWs w, int r) {
-  if (w.n_bad[r & 1] == 0) return;
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  const int n_t = min(*n_tracks_p, cap_tracks);
-  if (t >= n_t || !w.bad[t]) return;
-  const unsigned long long key = w.key[t];
-  for (long long k = off[t]; k < off[t + 1]; ++k) {
-    const int m = meas[k];
-    if (w.use[m] > 1) atomicMax(&w.slot_a[m], key);
+  int told = 0;  // reports that the others owe, over all steps so far
+  for (int r = 1, step = 1;; step = (step + 1) & 3) {  // steps 1, 2, 3 of round r, then step 0 of round r + 1
+    if (step == 1 && t == 0) poke(bad_count(w, r + 1), 0);  // (the round that used it last is over)
+    if (step == 0) ++r;
+    int team = 1;
+    if (need > 1) {
+      settle();
+      if (t == 0) sh = min(need, peek(w.joined));
+      __syncthreads();
+      team = sh;
+      told += team - 1;
+      if (t < kTailLines) poke(w.command + t * kLine, (r << 2 | step) << 18 | need << 9 | team);
+    }
+    res_step(q, w, buf, r, step, 0, team);
+    if (need > 1) {
+      settle();
+      if (t < 64) {
+        int reports;
+        do {
+          reports = t < kTailLines ? peek(w.done + t * kLine) : 0;
+#pragma unroll
+          for (int o = 32; o > 0; o >>= 1) reports += __shfl_xor(reports, o);
+        } while (reports != told);
+        settle();
+      }
+    }
+    __syncthreads();
+    if (step != 0) continue;
+    const int n = peek(bad_count(w, r));
+    const bool end = n == 0 || r == max_rounds;
+    const int now = end ? 1 : res_need(n);
+    if (need > 1 && now == 1 && t < kTailLines) poke(w.command + t * kLine, -1);
+    need = now;
+    if (!end) continue;
+    if (t == 0) {
+      *w.rounds = r;
+      *w.converged = n == 0 ? 1 : 0;
+    }
+    return;
   }
-}
-
-__global__ void k_res_claim_b(const int* __restrict__ n_tracks_p, int cap_tracks, const int* __restrict__ off,
-                              const int* __restrict__ meas, ResWs w, int r) {
-  if (w.n_bad[r & 1] == 0) return;
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  const int n_t = min(*n_tracks_p, cap_tracks);
-  if (t >= n_t || !w.bad[t]) return;
-  const unsigned long long key = w.key[t];
-  for (long long k = off[t]; k < off[t + 1]; ++k) {
-    const int m = meas[k];
-    if (w.use[m] > 1 && w.slot_a[m] == key) atomicMax(&w.slot_b[m], t);
-  }
-}
-
-__global__ void k_res_decide(const int* __restrict__ n_tracks_p, int cap_tracks, const int* __restrict__ off,
-                             const int* __restrict__ meas, ResWs w, int r) {
-  if (w.n_bad[r & 1] == 0) return;
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t == 0) ++*w.rounds;
-  const int n_t = min(*n_tracks_p, cap_tracks);
-  if (t >= n_t || !w.bad[t]) return;
-  const unsigned long long key = w.key[t];
-  bool top = true;
-  for (long long k = off[t]; top && k < off[t + 1]; ++k) {
-    const int m = meas[k];
-    if (w.use[m] > 1) top = w.slot_a[m] == key && w.slot_b[m] == t;
-  }
-  if (top) w.state[t] = 2;
-}
-
-__global__ void k_res_apply(const int* __restrict__ n_tracks_p, int cap_tracks, const int* __restrict__ off,
-                            const int* __restrict__ meas, ResWs w, int r) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t == 0) w.n_bad[(r + 1) & 1] = 0;  // the next round's count (the previous round's is no longer read)
-  if (w.n_bad[r & 1] == 0) return;
-  const int n_t = min(*n_tracks_p, cap_tracks);
-  if (t >= n_t) return;
-  if (w.state[t] != 2) return;
-  w.state[t] = 0;
-  for (long long k = off[t]; k < off[t + 1]; ++k) atomicSub(&w.use[meas[k]], 1);
 }
 
 __global__ void k_res_out(const int* __restrict__ n_tracks_p, int cap_tracks, ResWs w, int* __restrict__ keep,
-                          int* __restrict__ info, int r_last) {
+                          int* __restrict__ info) {
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t == 0 && info) {
     info[0] = *w.rounds;
-    info[1] = w.n_bad[r_last & 1] == 0 ? 1 : 0;
+    info[1] = *w.converged;
   }
   if (t >= cap_tracks) return;
   const int n_t = min(*n_tracks_p, cap_tracks);
@@ -194,10 +445,17 @@ ResWs res_view(void* ws, int cap_tracks, long long n_meas) {
   p += al256((size_t)cap_tracks * 8);
   w.state = reinterpret_cast<int*>(p);
   p += al256((size_t)cap_tracks * 4);
-  w.bad = reinterpret_cast<int*>(p);
-  p += al256((size_t)cap_tracks * 4);
-  w.n_bad = reinterpret_cast<int*>(p);
-  w.rounds = w.n_bad + 2;
+  for (int** l : {&w.list[0], &w.list[1]}) {
+    *l = reinterpret_cast<int*>(p);
+    p += al256((size_t)cap_tracks * 4);
+  }
+  int* word = reinterpret_cast<int*>(p);
+  w.n_list = word;
+  w.rounds = word + 4;
+  w.converged = word + 5;
+  w.joined = word + 6;
+  w.command = word + kLine;
+  w.done = w.command + kTailLines * kLine;
   return w;
 }
 
@@ -205,33 +463,32 @@ ResWs res_view(void* ws, int cap_tracks, long long n_meas) {
 
 size_t resolve_workspace_bytes(int cap_tracks, long long n_meas) {
   return al256((size_t)n_meas * 4) + al256((size_t)n_meas * 8) + al256((size_t)n_meas * 4) +
-         al256((size_t)cap_tracks * 8) + 2 * al256((size_t)cap_tracks * 4) + 256;  // last: n_bad[2], rounds
+         al256((size_t)cap_tracks * 8) + 3 * al256((size_t)cap_tracks * 4) + kResWords * 4;
 }
 
 hipError_t run_resolve(const int* n_tracks, int cap_tracks, long long cap_meas, const int* off, const int* meas,
                        long long n_meas, const double* chi2, const int* ndf, int max_shared, int max_rounds, void* ws,
                        int* keep, int* info, hipStream_t st) {
   const ResWs w = res_view(ws, cap_tracks, n_meas);
+  const ResTracks q{n_tracks, cap_tracks, off, meas, chi2, ndf, max_shared};
+  const dim3 block(kResBlock);
+  const auto grid = [](long long threads) { return dim3((unsigned)((threads + kResBlock - 1) / kResBlock)); };
   const long long n_init = n_meas > cap_tracks ? n_meas : (long long)cap_tracks;
-  hipLaunchKernelGGL(k_res_init, dim3((unsigned)((n_init + kResBlock) / kResBlock)), dim3(kResBlock), 0, st, n_meas,
-                     cap_tracks, w);
-  if (cap_tracks <= 0) {  // nothing to resolve (the track arrays may be NULL): report 0 rounds, converged
-    hipLaunchKernelGGL(k_res_out, dim3(1), dim3(kResBlock), 0, st, n_tracks, 0, w, keep, info, 0);
-    return hipGetLastError();
+  hipLaunchKernelGGL(k_res_init, grid(n_init + 1), block, 0, st, n_meas, cap_tracks, w);
+  const long long threads = (long long)cap_tracks * kResLanes;
+  if (cap_tracks > 0) {  // (else the track arrays may be NULL)
+    const dim3 all = grid(threads);
+    const int parts = (cap_tracks + kTailTracks - 1) / kTailTracks;
+    const dim3 grid_left(parts < 4 * kTailGrid ? parts : 4 * kTailGrid);
+    hipLaunchKernelGGL(k_res_count, all, block, 0, st, q, cap_meas, n_meas, w);
+    hipLaunchKernelGGL(k_res_shared, all, block, 0, st, q, w);
+    hipLaunchKernelGGL(k_res_step<1>, all, block, 0, st, q, w);
+    hipLaunchKernelGGL(k_res_step<2>, all, block, 0, st, q, w);
+    hipLaunchKernelGGL(k_res_step<3>, all, block, 0, st, q, w);
+    hipLaunchKernelGGL(k_res_left, grid_left, dim3(kTailBlock), 0, st, q, w);
   }
-  const dim3 grid((cap_tracks + kResBlock - 1) / kResBlock), block(kResBlock);
-  hipLaunchKernelGGL(k_res_count, grid, block, 0, st, n_tracks, cap_tracks, cap_meas, off, meas, n_meas, w);
-  for (int r = 0; r < max_rounds; ++r) {
-    hipLaunchKernelGGL(k_res_shared, grid, block, 0, st, n_tracks, cap_tracks, off, meas, chi2, ndf, max_shared, w, r);
-    hipLaunchKernelGGL(k_res_claim_a, grid, block, 0, st, n_tracks, cap_tracks, off, meas, w, r);
-    hipLaunchKernelGGL(k_res_claim_b, grid, block, 0, st, n_tracks, cap_tracks, off, meas, w, r);
-    hipLaunchKernelGGL(k_res_decide, grid, block, 0, st, n_tracks, cap_tracks, off, meas, w, r);
-    hipLaunchKernelGGL(k_res_apply, grid, block, 0, st, n_tracks, cap_tracks, off, meas, w, r);
-  }
-  // is any bad track left after the last round?
-  hipLaunchKernelGGL(k_res_shared, grid, block, 0, st, n_tracks, cap_tracks, off, meas, chi2, ndf, max_shared, w,
-                     max_rounds);
-  hipLaunchKernelGGL(k_res_out, grid, block, 0, st, n_tracks, cap_tracks, w, keep, info, max_rounds);
+  hipLaunchKernelGGL(k_res_tail, dim3(cap_tracks > 0 ? kTailGrid : 1), dim3(kTailBlock), 0, st, q, w, max_rounds);
+  hipLaunchKernelGGL(k_res_out, grid(cap_tracks + 1), block, 0, st, n_tracks, cap_tracks, w, keep, info);
   return hipGetLastError();
 }
 

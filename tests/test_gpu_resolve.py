@@ -167,3 +167,54 @@ def test_resolve_round_bound_and_graph_capture(ckf):
         torch.cuda.synchronize()
         assert np.array_equal(kg.cpu().numpy(), keep_o), rep
         assert list(info.cpu().numpy()) == [rounds, 1], rep
+
+
+def _rounds(off, meas, chi2, ndf, n_m, max_shared, max_rounds):
+    """The parallel rounds, in numpy: kept tracks, rounds, converged."""
+    n = np.diff(off)
+    tr = np.repeat(np.arange(len(n)), n)
+    live = np.ones(len(n), bool)
+    q = (chi2.astype(np.float32) / np.maximum(ndf, 1).astype(np.float32)).view(np.uint32).astype(np.int64)
+    for r in range(max_rounds + 1):
+        use = np.bincount(meas[live[tr]], minlength=n_m)
+        s = np.bincount(tr, weights=use[meas] > 1, minlength=len(n)).astype(np.int64)
+        bad = live & (s > max_shared)
+        if not bad.any() or r == max_rounds:
+            return live, r, not bad.any()
+        rank = np.empty(len(n), np.int64)
+        rank[np.lexsort((np.arange(len(n)), q, (s << 31) // n))] = np.arange(len(n))
+        at = bad[tr]
+        top = np.full(n_m, -1)
+        np.maximum.at(top, meas[at], rank[tr[at]])
+        lost = np.zeros(len(n), bool)
+        lost[tr[at][top[meas[at]] != rank[tr[at]]]] = True
+        live = live & ~(bad & ~lost)
+
+
+@pytest.mark.parametrize("kind, n_t, max_rounds", [("chain", 1, 8), ("chain", 2, 8), ("chain", 33, 128), ("chain", 200, 1),
+                                                   ("chain", 200, 2), ("chain", 200, 1024), ("chain", 600, 128),
+                                                   ("random", 3000, 3), ("random", 40000, 1024), ("long", 300, 1024)])
+def test_resolve_rounds(ckf, kind, n_t, max_rounds):
+    """Few and many bad tracks over few and many rounds, cut off or not, and
+    tracks of fewer and more measurements than a group of lanes: the kept
+    set, the number of rounds and the flag are those of the same rounds in
+    numpy.  In a chain each track shares two measurements with the next one
+    and the keys rise along it, so that a round removes one track."""
+    rng = np.random.default_rng(n_t + max_rounds)
+    if kind == "chain":
+        off = np.arange(n_t + 1, dtype=np.int32) * 10
+        meas = (np.arange(n_t)[:, None] * 8 + np.arange(10)[None]).astype(np.int32).ravel()
+        n_m, chi2, ndf = 8 * n_t + 2, 1.0 + np.arange(n_t), np.full(n_t, 15, np.int32)
+    elif kind == "random":
+        off, meas, chi2, ndf, n_m = _random_set(rng, n_t, int(1.5 * n_t), 40)
+    else:
+        n = rng.integers(1, 40, n_t)
+        off = np.r_[0, np.cumsum(n)].astype(np.int32)
+        n_m = 4 * n_t
+        meas = np.concatenate([rng.choice(n_m, k, replace=False) for k in n]).astype(np.int32)
+        chi2, ndf = rng.uniform(1, 50, n_t), np.maximum(1, 2 * n - 5).astype(np.int32)
+    keep, info = ckf.resolve(_dev_tracks(off, meas, chi2, ndf), n_m, max_rounds=max_rounds, sync=False)
+    ref, rounds, done = _rounds(off.astype(np.int64), meas, chi2, ndf, n_m, 1, max_rounds)
+    _say(f"# {kind} of {n_t}: {rounds} rounds, keeps {int(ref.sum())}")
+    np.testing.assert_array_equal(keep.cpu().numpy() == 1, ref)
+    assert list(info.cpu().numpy()) == [rounds, int(done)]
