@@ -569,7 +569,8 @@ def seed(geometry: Geometry, n_events: int, meas_offsets, spacepoints, loc, laye
            "ckf_seed_workspace_size")
     ws = torch.empty(max(1, int(nb.value)), dtype=torch.uint8, device=dev)
     cap = int(cap_seeds) if cap_seeds is not None else max(1, 2 * n_sp)
-    z = lambda shape, dt: torch.zeros(shape, dtype=dt, device=dev)
+    # (the call writes the count and every row that is returned)
+    z = lambda shape, dt: torch.empty(shape, dtype=dt, device=dev)
     out = dict(event=z(cap, torch.int32), surface=z(cap, torch.int32), params=z((cap, 5), torch.float64),
                cov=z((cap, 15), torch.float64), spacepoints=z((cap, 3), torch.int32))
     n = z(1, torch.int32)

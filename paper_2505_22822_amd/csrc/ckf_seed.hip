@@ -7,7 +7,7 @@
 // layout (rows of (event, module)).  The seeding layers are a list ordered
 // outwards.  The kernels:
 //   rows    - every spacepoint's row by a max-scan of row heads;
-//   bin     - spacepoints of seeding layers keyed by (event, layer, phi bin,
+//   bin     - spacepoints of seeding layers keyed by (layer, event, phi bin,
 //             z bin) and counted, each layer's radius range taken; a
 //             sum-scan gives the bins' starts; a placement pass fills them
 //             and copies the points in that order with their radius (order
@@ -52,6 +52,8 @@ constexpr double kCotMax = 3.0, kZ0Max = 200.0, kPtMin = 0.5, kD0Max = 1.0, kDco
 constexpr double kSigma[5] = {0.2, 0.6, 0.01, 0.01, 0.15};
 constexpr double kTolMax = kDcotBase + kDcotMs * (1.0 + kCotMax * kCotMax);  // the largest cot tolerance
 constexpr int kTriGrid = 1024;  // persistent workgroups of the triplet search: 4 per CU, a multiple of the 8 XCDs
+constexpr int kXcds = 8;
+constexpr int kLine = 32;       // ints from one XCD's queue counter to the next (a line each)
 
 struct SeedLayers {
   int n;
@@ -65,12 +67,13 @@ __global__ void k_sd_heads(long long rows, const int* __restrict__ moff, long lo
   if (a >= 0 && a < b && (long long)b <= n_sp) head[a] = (int)r;
 }
 
-__global__ void k_sd_fill(long long n, int* __restrict__ head, int* __restrict__ cnt, int nbins,
-                          unsigned* __restrict__ rlim) {
+__global__ void k_sd_fill(long long n, int* __restrict__ head, int* __restrict__ cnt, int* __restrict__ fill,
+                          long long nbins, unsigned* __restrict__ rlim, int* __restrict__ queue) {
   const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) head[i] = -1;
-  if (i < nbins) cnt[i] = 0;
-  if (rlim && i < kMaxSeedLayers) {
+  if (i < nbins) cnt[i] = fill[i] = 0;
+  if (i < kXcds * kLine) queue[i] = 0;
+  if (i < kMaxSeedLayers) {
     rlim[2 * i] = 0x7f800000u;  // +inf: minimum radius of the layer's spacepoints
     rlim[2 * i + 1] = 0u;       // maximum
   }
@@ -88,7 +91,7 @@ __device__ __forceinline__ int phi_bin(double x, double y) {
 }
 
 // key of every spacepoint (-1: not on a seeding layer) and the bin counts
-__global__ void __launch_bounds__(kSdBlock) k_sd_key(long long n, int n_surfaces, GeomDev g, SeedLayers sl,
+__global__ void __launch_bounds__(kSdBlock) k_sd_key(long long n, int n_events, int n_surfaces, GeomDev g, SeedLayers sl,
                                                      const int* __restrict__ row, const float* __restrict__ xyz,
                                                      int* __restrict__ key, int* __restrict__ cnt,
                                                      unsigned* __restrict__ rlim) {
@@ -109,7 +112,7 @@ __global__ void __launch_bounds__(kSdBlock) k_sd_key(long long n, int n_surfaces
       if (sl.layer[q] == M.layer) li = q;
     if (li >= 0) {
       const double x = xyz[3 * i], y = xyz[3 * i + 1];
-      k = ((e * sl.n + li) * kNphi + phi_bin(x, y)) * kNz + z_bin(xyz[3 * i + 2]);
+      k = ((li * n_events + e) * kNphi + phi_bin(x, y)) * kNz + z_bin(xyz[3 * i + 2]);
       atomicAdd(&cnt[k], 1);
       const float r = (float)sqrt(x * x + y * y);  // radius bounds (positive floats order as their bits)
       atomicMin(&s_lim[2 * li], __float_as_uint(r));
@@ -192,27 +195,39 @@ __device__ __forceinline__ void z_window(double a00, double a01, double a10, dou
   b1 = z_bin(hi);
 }
 
-// One wave per middle spacepoint M (a persistent grid walks the binned
-// spacepoints in sorted order, so the waves of one XCD work on neighbouring
-// middles at the same time).  For M:
+// One wave per middle spacepoint M.  The middles are one range of the sorted
+// order, dealt to the 8 XCDs in runs of kRun neighbours; the waves of a
+// persistent grid take an XCD's middles one after the other from a counter.
+// (With a fixed share per wave, the waves' middles of unequal work kept a
+// wave busy for 72 % of the kernel's time on average.)  For M:
+//   0. a lane per (layer, phi bin) range: the z window in which its
+//      candidates lie, and the range's ends in the sorted order;
 //   1. its tops: spacepoints of higher layers in M's and the two neighbouring
 //      phi bins and in the z window of |cot| <= COT_MAX.  The lanes split
-//      them; a first pass counts the ones passing the (M, T) doublet cuts per
-//      cot bucket, a second pass (the same arithmetic, so the same results)
-//      writes their (cot, index) into LDS in bucket order;
+//      them; the ones passing the (M, T) doublet cuts are listed in LDS with
+//      their cot and counted per cot bucket, and then put into bucket order;
 //   2. its bottoms, split over the lanes like the tops.  Bottoms passing the
 //      (B, M) cuts enter a wave queue; each batch of 64 gives every lane one
 //      bottom, which walks the tops of the buckets around cot_BM +- tol and
 //      puts the (B, T) pairs within the cot cut into a second wave queue;
-//      each batch of 64 pairs gets the circle and d0 cuts, one pair per lane.
-//      So the expensive tests run on full waves;
+//      each batch of 64 pairs gets a test without divisions that rejects
+//      most of those that fail the circle and d0 cuts (19 of 20 pairs fail)
+//      and no other, and the rest enter a third queue for the cuts as
+//      defined, one pair per lane.  So the expensive tests run on full waves;
 //   3. each lane keeps its best KEEP by (d0, B, T); a wave reduction takes the
 //      best KEEP of the middle.
 // More passing tops than the LDS holds: each bottom then scans the tops of
 // its z window directly (the same cuts, no buckets, no queues).
+//
+// Bound by vector instructions; 40 KB of LDS and at most 128 registers put
+// four workgroups on a CU.  One mu = 200 event (20 000 middles, 15.4M doublet
+// tests, 12.9M pairs): 307 -> 227 us, with 111M -> 82M vector instructions.
 constexpr int kTriWaves = 4;          // waves per workgroup
 constexpr int kTopCap = 608;          // passing tops of one middle held in LDS (at most)
-constexpr int kRing = 128;            // capacity of each wave queue (a power of two >= 127)
+constexpr int kTopRounds = (kTopCap + 63) / 64;
+constexpr int kRing = 128;            // capacity of a wave queue (a power of two >= 127)
+constexpr int kPick = 96;             // capacity of the third: up to 32 left over and 64 new ones
+constexpr int kRun = 16;
 constexpr double kCotBucket = 0.025;  // cot bucket width
 constexpr int kNcot = 241;            // buckets over [-COT_MAX, COT_MAX] (cot = COT_MAX lands in the last)
 constexpr int kNcotPad = 256;         // 4 per lane for the scan
@@ -258,130 +273,218 @@ __device__ __forceinline__ void try_triplet(const P3& B, int b, const P3& M, con
   keep_best(best, Cand{d0, b, t});
 }
 
-__global__ void __launch_bounds__(64 * kTriWaves) k_sd_triplets(
-    long long nbins, SeedLayers sl, const int* __restrict__ key, const int* __restrict__ start,
+// What the reject test needs of a middle.
+struct Middle2 {
+  double x, y, r2;
+  double noise;  // bound on |d| times the rounding of the cuts' R and d0
+  double rmin;
+};
+
+// False only if (B, M, T) fails the circle or d0 cut.  With p = B - M, q =
+// T - M, d = 2 p x q and N = d (u - M), u the circle's centre: R = |N| / |d|,
+// and d0 = | |u| - R | = |2 M.N + M^2 d| / (|d| (|u| + R)), where |d| |u| =
+// |N + M d|.  The square roots and products here are good to 1e-7; the cuts'
+// own rounding moves R and d0 by at most noise / |d| (the numerators of their
+// u are sums of products up to 2 r^3, r the largest radius: 1e-12 r^3 is far
+// above 64 roundings of that), so a pair is rejected only if it fails by more
+// than both.  NaNs are not rejected.
+__device__ __forceinline__ bool maybe_triplet(const Middle2& M, const double2& b, const double2& t) {
+  const double px = b.x - M.x, py = b.y - M.y, qx = t.x - M.x, qy = t.y - M.y;
+  const double pp = __builtin_fma(px, px, py * py), qq = __builtin_fma(qx, qx, qy * qy);
+  const double d = 2.0 * __builtin_fma(px, qy, -(py * qx));
+  const double nx = __builtin_fma(pp, qy, -(qq * py)), ny = __builtin_fma(qq, px, -(pp * qx));
+  const double ux = __builtin_fma(M.x, d, nx), uy = __builtin_fma(M.y, d, ny);
+  const double n = __builtin_amdgcn_sqrt(__builtin_fma(nx, nx, ny * ny));
+  const double u = __builtin_amdgcn_sqrt(__builtin_fma(ux, ux, uy * uy));
+  const double x = fabs(__builtin_fma(2.0, __builtin_fma(M.x, nx, M.y * ny), M.r2 * d)), ad = fabs(d);
+  if (__builtin_fma(n, 1.00001, M.noise) < M.rmin * ad) return false;
+  return !(x * ad > (n + u) * __builtin_fma(ad, 1.00001 * kD0Max, M.noise));
+}
+
+__global__ void __launch_bounds__(64 * kTriWaves, 4) k_sd_triplets(
+    int n_events, SeedLayers sl, const int* __restrict__ key, const int* __restrict__ start,
     const int* __restrict__ cnt, const int* __restrict__ sorted, const double4* __restrict__ spt,
-    const unsigned* __restrict__ rlim, double rmin, double tan_dphi, int top_cap, int* __restrict__ count,
-    int2* __restrict__ best_out, unsigned long long* __restrict__ work) {
+    const unsigned* __restrict__ rlim, int* __restrict__ queue, double rmin, double tan_dphi, int top_cap,
+    int* __restrict__ count, int2* __restrict__ best_out, unsigned long long* __restrict__ work) {
   __shared__ double s_ct[kTriWaves][kTopCap];
   __shared__ int s_j[kTriWaves][kTopCap];
   __shared__ int s_bs[kTriWaves][kNcotPad];
   __shared__ int s_bq[kTriWaves][kRing];
-  __shared__ int2 s_pq[kTriWaves][kRing];
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  __shared__ int s_pb[kTriWaves][kRing], s_cb[kTriWaves][kPick];
+  __shared__ unsigned short s_pt[kTriWaves][kRing], s_ck[kTriWaves][kPick];
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   double* ct_s = s_ct[w];
   int* j_s = s_j[w];
   int* bs = s_bs[w];
   int* bq = s_bq[w];
-  int2* pq = s_pq[w];
-  // XCD-aware numbering: workgroups are dealt round-robin to the 8 XCDs, so
-  // consecutive logical waves are put on one XCD
-  const int G = gridDim.x, xcd = blockIdx.x % 8, per = G / 8;
-  const int lblock = (G % 8 == 0) ? xcd * per + blockIdx.x / 8 : blockIdx.x;
-  const long long W = (long long)G * kTriWaves;
-  const long long total = nbins > 0 ? (long long)start[nbins - 1] + cnt[nbins - 1] : 0;
+  int* pb_q = s_pb[w];              // pairs: the bottom, and the top's place in the bucket order
+  unsigned short* pt_q = s_pt[w];
+  int* cb_q = s_cb[w];
+  unsigned short* ct_q = s_ck[w];
+  if (sl.n < 3) return;  // no inner layer (the work counters are cleared already)
+  static_assert(kTriGrid % kXcds == 0, "workgroups are dealt round-robin to the XCDs");
+  const int xcd = blockIdx.x % kXcds;
+  const long long lo = start[n_events * kNphi * kNz], n_mid = start[(sl.n - 1) * n_events * kNphi * kNz] - lo;
+  double r_out = 0.0;
+  for (int q = 0; q < sl.n; ++q) r_out = fmax(r_out, (double)__uint_as_float(rlim[2 * q + 1]));
+  const double noise = 1e-12 * r_out * r_out * r_out;
   // this lane's work units: (M, T) and (B, M) doublet tests, (B, T) cot
   // comparisons, triplet (circle) tests
   unsigned n_mt = 0, n_bm = 0, n_cot = 0, n_tri = 0;
-  for (long long j = (long long)lblock * kTriWaves + w; j < total; j += W) {
+  int next = 0;
+  for (int i = (blockIdx.x / kXcds) * kTriWaves + w;; i = gridDim.x / kXcds * kTriWaves + __builtin_amdgcn_readfirstlane(next)) {
+    const long long run = ((long long)(i / kRun) * kXcds + xcd) * kRun, at = run + i % kRun;
+    if (run >= n_mid) break;
+    if (lane == 0) next = atomicAdd(queue + xcd * kLine, 1);  // (the next middle's number, in flight meanwhile)
+    if (at >= n_mid) continue;
+    const long long j = lo + at;
     const int m = sorted[j];
     const int km = key[m];
-    const int bin_m = (km / kNz) % kNphi, li_m = (km / (kNz * kNphi)) % sl.n, e = km / (kNz * kNphi * sl.n);
-    if (li_m == 0 || li_m == sl.n - 1) continue;
+    const int bin_m = (km / kNz) % kNphi, e = (km / (kNz * kNphi)) % n_events, li_m = km / (kNz * kNphi * n_events);
     const double4 pm = spt[j];
     const P3 M{pm.x, pm.y, pm.z};
     const double rM = pm.w;
+    const Middle2 M2{M.x, M.y, M.x * M.x + M.y * M.y, noise, rmin};
     const auto range = [&](int layer, int dphi, int z0, int z1, int& j0, int& j1) {
-      // consecutive z bins of one (event, layer, phi bin) are adjacent in the
+      // consecutive z bins of one (layer, event, phi bin) are adjacent in the
       // sorted order: a z window is one range
-      const int k0 = ((e * sl.n + layer) * kNphi + (bin_m + dphi + kNphi) % kNphi) * kNz;
+      const int k0 = ((layer * n_events + e) * kNphi + (bin_m + dphi + kNphi) % kNphi) * kNz;
       j0 = start[k0 + z0];
       j1 = start[k0 + z1] + cnt[k0 + z1];
     };
-    // every top candidate of M through the (M, T) doublet cuts; place = false
-    // counts the passing ones per bucket, place = true writes them in bucket
-    // order (bs holds the buckets' starts then, and their ends afterwards)
-    // A top of a triplet has |cot_MT| <= COT_MAX and, since the bottom's
-    // doublet line meets z0 = z_M - r_M cot_BM within Z0_MAX and cot_MT is
-    // within tol <= kTolMax of cot_BM, |z_M - r_M cot_MT| <= Z0_MAX + r_M
-    // kTolMax: the cot window of the tops (1 mm of margin)
-    const double zb = kZ0Max + kTolMax * rM + kZMargin;
-    const double clo = fmax(-kCotMax, (M.z - zb) / rM), chi = fmin(kCotMax, (M.z + zb) / rM);
-    const auto tops = [&](bool place) {
-      int n = 0;
-      for (int lt = li_m + 1; lt < sl.n; ++lt) {
-        const double s0 = __uint_as_float(rlim[2 * lt]) - rM, s1 = __uint_as_float(rlim[2 * lt + 1]) - rM;
-        if (!(s0 <= s1) || !(clo <= chi)) continue;
-        int zt0, zt1;
-        z_window(M.z + s0 * clo, M.z + s0 * chi, M.z + s1 * clo, M.z + s1 * chi, zt0, zt1);
-        for (int dt = -1; dt <= 1; ++dt) {
-          int j0, j1;
-          range(lt, dt, zt0, zt1, j0, j1);
-          for (int base = j0; base < j1; base += 64) {
-            const int jt = base + lane;
-            bool pass = false;
-            double ct = 0.0;
-            if (jt < j1) {
-              const double4 pt = spt[jt];
-              pass = doublet(M, rM, P3{pt.x, pt.y, pt.z}, pt.w, false, tan_dphi, ct);
-              if (!place) ++n_mt;  // (the placing pass repeats the same tests)
-            }
-            if (pass) {
-              if (!place) {
-                atomicAdd(&bs[cot_bucket(ct)], 1);
-              } else {
-                const int pos = atomicAdd(&bs[cot_bucket(ct)], 1);
-                ct_s[pos] = ct;
-                j_s[pos] = jt;
-              }
-            }
-            n += __popcll(__ballot(pass));
-          }
-        }
+    // 0. ranges.  A top of a triplet has |cot_MT| <= COT_MAX and, since the
+    // bottom's doublet line meets z0 = z_M - r_M cot_BM within Z0_MAX and
+    // cot_MT is within tol <= kTolMax of cot_BM, |z_M - r_M cot_MT| <= Z0_MAX +
+    // r_M kTolMax: the cot window of the tops (1 mm of margin)
+    const int n_range = 3 * (sl.n - 1), n_low = 3 * li_m;  // bottoms' ranges, then tops'
+    int r0 = 0, r1 = 0;
+    if (lane < n_range) {
+      const int layer = lane / 3 + (lane >= n_low ? 1 : 0);
+      const double a = __uint_as_float(rlim[2 * layer]), b = __uint_as_float(rlim[2 * layer + 1]);
+      int z0, z1;
+      bool some;
+      if (lane >= n_low) {
+        const double zb = kZ0Max + kTolMax * rM + kZMargin;
+        const double clo = fmax(-kCotMax, (M.z - zb) / rM), chi = fmin(kCotMax, (M.z + zb) / rM);
+        const double s0 = a - rM, s1 = b - rM;
+        some = s0 <= s1 && clo <= chi;
+        z_window(M.z + s0 * clo, M.z + s0 * chi, M.z + s1 * clo, M.z + s1 * chi, z0, z1);
+      } else {
+        // z_B = z0 + r_B (z_M - z0) / r_M for |z0| <= Z0_MAX, r_B in the layer's range
+        z_window(-kZ0Max + a * (M.z + kZ0Max) / rM, kZ0Max + a * (M.z - kZ0Max) / rM,
+                 -kZ0Max + b * (M.z + kZ0Max) / rM, kZ0Max + b * (M.z - kZ0Max) / rM, z0, z1);
+        // and |cot_BM| <= COT_MAX: z_B = z_M - (r_M - r_B) cot_BM
+        int c0, c1;
+        z_window(M.z - kCotMax * (rM - a), M.z + kCotMax * (rM - a), M.z - kCotMax * (rM - b),
+                 M.z + kCotMax * (rM - b), c0, c1);
+        z0 = max(z0, c0);
+        z1 = min(z1, c1);
+        some = a <= b && z0 <= z1;
       }
-      return n;
-    };
+      if (some) range(layer, lane % 3 - 1, z0, z1, r0, r1);
+    }
     wave_sync();  // the previous middle's LDS reads are done
-    // 1. tops: count per bucket, scan, place
+    // 1. tops: list, count per bucket, scan, place
     for (int q = lane; q < kNcotPad; q += 64) bs[q] = 0;
-    wave_sync();
-    const int n_top = tops(false);
+    int n_top = 0;
+    for (int q = n_low; q < n_range; ++q) {
+      const int j1 = __builtin_amdgcn_readlane(r1, q);
+      for (int base = __builtin_amdgcn_readlane(r0, q); base < j1; base += 64) {
+        const int jt = base + lane;
+        bool pass = false;
+        double ct = 0.0;
+        if (jt < j1) {
+          const double4 pt = spt[jt];
+          pass = doublet(M, rM, P3{pt.x, pt.y, pt.z}, pt.w, false, tan_dphi, ct);
+          ++n_mt;
+        }
+        const unsigned long long mask = __ballot(pass);
+        const int pos = n_top + lanes_below(mask);
+        if (pass && pos < kTopCap) {
+          ct_s[pos] = ct;
+          j_s[pos] = jt;
+        }
+        n_top += __popcll(mask);
+      }
+    }
     const bool in_lds = n_top <= top_cap;
+    wave_sync();
     if (in_lds) {
+      double ct[kTopRounds];
+      int jt[kTopRounds], slot[kTopRounds];  // slot: bucket, rank in it
+#pragma unroll
+      for (int q = 0; q < kTopRounds; ++q) {
+        if (64 * q < n_top && 64 * q + lane < n_top) {
+          ct[q] = ct_s[64 * q + lane];
+          jt[q] = j_s[64 * q + lane];
+          const int k = cot_bucket(ct[q]);
+          slot[q] = k << 16 | atomicAdd(&bs[k], 1);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
       wave_sync();
       const int v0 = bs[4 * lane], v1 = bs[4 * lane + 1], v2 = bs[4 * lane + 2], v3 = bs[4 * lane + 3];
-      const int sum = v0 + v1 + v2 + v3;
-      int incl = sum;
+      int incl = v0 + v1 + v2 + v3;
 #pragma unroll
       for (int off = 1; off < 64; off <<= 1) {
         const int t = __shfl_up(incl, off);
         if (lane >= off) incl += t;
       }
-      const int ex = incl - sum;
-      bs[4 * lane] = ex;
-      bs[4 * lane + 1] = ex + v0;
-      bs[4 * lane + 2] = ex + v0 + v1;
-      bs[4 * lane + 3] = ex + v0 + v1 + v2;
+      bs[4 * lane] = incl - v3 - v2 - v1;  // the buckets' ends
+      bs[4 * lane + 1] = incl - v3 - v2;
+      bs[4 * lane + 2] = incl - v3;
+      bs[4 * lane + 3] = incl;
       wave_sync();
-      tops(true);
+#pragma unroll
+      for (int q = 0; q < kTopRounds; ++q) {
+        if (64 * q < n_top && 64 * q + lane < n_top) {
+          const int k = slot[q] >> 16, pos = (k > 0 ? bs[k - 1] : 0) + (slot[q] & 0xffff);
+          ct_s[pos] = ct[q];
+          j_s[pos] = jt[q];
+        }
+      }
       wave_sync();
     }
     Cand best[kKeep];
 #pragma unroll
     for (int k = 0; k < kKeep; ++k) best[k] = Cand{INFINITY, -1, -1};
     // 2. bottoms
-    int btail = 0, bhead = 0, ptail = 0, phead = 0;  // queue positions (the same in every lane)
-    // up to 64 queued pairs, one per lane, through the circle and d0 cuts
+    int btail = 0, bhead = 0, ptail = 0, phead = 0, picked = 0;  // queue positions (the same in every lane)
+    // the picked pairs, one per lane, through the circle and d0 cuts
+    const auto run_picked = [&]() {
+      wave_sync();
+      while (picked > 0) {
+        const int np = min(64, picked);
+        picked -= np;
+        if (lane < np) {
+          const int jb = cb_q[picked + lane], jt = j_s[ct_q[picked + lane]];
+          const double4 pb = spt[jb];
+          try_triplet(P3{pb.x, pb.y, pb.z}, sorted[jb], M, spt[jt], sorted[jt], rmin, best);
+        }
+      }
+      wave_sync();
+    };
+    // up to 64 queued pairs, one per lane, through the reject test
     const auto run_pairs = [&]() {
       wave_sync();
       const int np = min(64, ptail - phead);
+      bool pick = false;
+      int jb = 0, slot = 0;
       if (lane < np) {
         ++n_tri;
-        const int2 q = pq[(phead + lane) & (kRing - 1)];
-        const double4 pb = spt[q.x];
-        try_triplet(P3{pb.x, pb.y, pb.z}, sorted[q.x], M, spt[q.y], sorted[q.y], rmin, best);
+        jb = pb_q[(phead + lane) & (kRing - 1)];
+        slot = pt_q[(phead + lane) & (kRing - 1)];
+        pick = maybe_triplet(M2, *reinterpret_cast<const double2*>(spt + jb),
+                             *reinterpret_cast<const double2*>(spt + j_s[slot]));
       }
+      const unsigned long long mask = __ballot(pick);
+      if (pick) {
+        cb_q[picked + lanes_below(mask)] = jb;
+        ct_q[picked + lanes_below(mask)] = (unsigned short)slot;
+      }
+      picked += __popcll(mask);
       phead += np;
+      if (picked > kPick - 64) run_picked();
       wave_sync();
     };
     // up to 64 queued bottoms, one per lane, walk their cot window
@@ -402,80 +505,67 @@ __global__ void __launch_bounds__(64 * kTriWaves) k_sd_triplets(
       bhead += nb;
       while (__any(p < p1)) {
         bool hit = false;
-        int jt = 0;
         if (p < p1) {
           ++n_cot;
           hit = fabs(cb - ct_s[p]) <= tol;
-          jt = j_s[p];
           ++p;
         }
         const unsigned long long mask = __ballot(hit);
-        if (hit) pq[(ptail + lanes_below(mask)) & (kRing - 1)] = make_int2(jb, jt);
+        if (hit) {
+          const int at = (ptail + lanes_below(mask)) & (kRing - 1);
+          pb_q[at] = jb;
+          pt_q[at] = (unsigned short)(p - 1);
+        }
         ptail += __popcll(mask);
         if (ptail - phead >= 64) run_pairs();
       }
     };
-    for (int lb = 0; lb < li_m; ++lb) {
-      // z_B = z0 + r_B (z_M - z0) / r_M for |z0| <= Z0_MAX, r_B in the layer's range
-      const double r0 = __uint_as_float(rlim[2 * lb]), r1 = __uint_as_float(rlim[2 * lb + 1]);
-      if (!(r0 <= r1)) continue;  // no spacepoints on that layer
-      int zb0, zb1, zc0, zc1;
-      z_window(-kZ0Max + r0 * (M.z + kZ0Max) / rM, kZ0Max + r0 * (M.z - kZ0Max) / rM,
-               -kZ0Max + r1 * (M.z + kZ0Max) / rM, kZ0Max + r1 * (M.z - kZ0Max) / rM, zb0, zb1);
-      // and |cot_BM| <= COT_MAX: z_B = z_M - (r_M - r_B) cot_BM
-      z_window(M.z - kCotMax * (rM - r0), M.z + kCotMax * (rM - r0), M.z - kCotMax * (rM - r1),
-               M.z + kCotMax * (rM - r1), zc0, zc1);
-      zb0 = max(zb0, zc0);
-      zb1 = min(zb1, zc1);
-      if (zb0 > zb1) continue;
-      for (int db = -1; db <= 1; ++db) {
-        int j0, j1;
-        range(lb, db, zb0, zb1, j0, j1);
-        if (in_lds) {
-          for (int base = j0; base < j1; base += 64) {
-            const int jb = base + lane;
-            bool pass = false;
-            if (jb < j1) {
-              const double4 pb = spt[jb];
-              double cb;
-              pass = doublet(P3{pb.x, pb.y, pb.z}, pb.w, M, rM, true, tan_dphi, cb);
-              ++n_bm;
-            }
-            const unsigned long long mask = __ballot(pass);
-            if (pass) bq[(btail + lanes_below(mask)) & (kRing - 1)] = jb;
-            btail += __popcll(mask);
-            if (btail - bhead >= 64) run_bottoms();
+    for (int q = 0; q < n_low; ++q) {
+      const int j0 = __builtin_amdgcn_readlane(r0, q), j1 = __builtin_amdgcn_readlane(r1, q);
+      if (in_lds) {
+        for (int base = j0; base < j1; base += 64) {
+          const int jb = base + lane;
+          bool pass = false;
+          if (jb < j1) {
+            const double4 pb = spt[jb];
+            double cb;
+            pass = doublet(P3{pb.x, pb.y, pb.z}, pb.w, M, rM, true, tan_dphi, cb);
+            ++n_bm;
           }
-          continue;
+          const unsigned long long mask = __ballot(pass);
+          if (pass) bq[(btail + lanes_below(mask)) & (kRing - 1)] = jb;
+          btail += __popcll(mask);
+          if (btail - bhead >= 64) run_bottoms();
         }
-        for (int jb = j0 + lane; jb < j1; jb += 64) {
-          const double4 pb = spt[jb];
-          const P3 B{pb.x, pb.y, pb.z};
-          double cb;
-          ++n_bm;
-          if (!doublet(B, pb.w, M, rM, true, tan_dphi, cb)) continue;
-          const int b = sorted[jb];
-          const double tol = kDcotBase + kDcotMs * (1.0 + cb * cb);
-          for (int lt = li_m + 1; lt < sl.n; ++lt) {
-            // z_T = z_M + (r_T - r_M) cot_T for cot_T within tol of cot_BM
-            const double s0 = __uint_as_float(rlim[2 * lt]) - rM, s1 = __uint_as_float(rlim[2 * lt + 1]) - rM;
-            if (!(s0 <= s1)) continue;
-            int zt0, zt1;
-            z_window(M.z + s0 * (cb - tol), M.z + s0 * (cb + tol), M.z + s1 * (cb - tol), M.z + s1 * (cb + tol),
-                     zt0, zt1);
-            for (int dt = -1; dt <= 1; ++dt) {
-              int t0, t1;
-              range(lt, dt, zt0, zt1, t0, t1);
-              for (int jt = t0; jt < t1; ++jt) {
-                const double4 pt = spt[jt];
-                double ct;
-                ++n_mt;
-                if (!doublet(M, rM, P3{pt.x, pt.y, pt.z}, pt.w, false, tan_dphi, ct)) continue;
-                ++n_cot;
-                if (!(fabs(cb - ct) <= tol)) continue;
-                ++n_tri;
-                try_triplet(B, b, M, pt, sorted[jt], rmin, best);
-              }
+        continue;
+      }
+      for (int jb = j0 + lane; jb < j1; jb += 64) {
+        const double4 pb = spt[jb];
+        const P3 B{pb.x, pb.y, pb.z};
+        double cb;
+        ++n_bm;
+        if (!doublet(B, pb.w, M, rM, true, tan_dphi, cb)) continue;
+        const int b = sorted[jb];
+        const double tol = kDcotBase + kDcotMs * (1.0 + cb * cb);
+        for (int lt = li_m + 1; lt < sl.n; ++lt) {
+          // z_T = z_M + (r_T - r_M) cot_T for cot_T within tol of cot_BM
+          const double s0 = __uint_as_float(rlim[2 * lt]) - rM, s1 = __uint_as_float(rlim[2 * lt + 1]) - rM;
+          if (!(s0 <= s1)) continue;
+          int zt0, zt1;
+          z_window(M.z + s0 * (cb - tol), M.z + s0 * (cb + tol), M.z + s1 * (cb - tol), M.z + s1 * (cb + tol),
+                   zt0, zt1);
+          for (int dt = -1; dt <= 1; ++dt) {
+            int t0, t1;
+            range(lt, dt, zt0, zt1, t0, t1);
+            for (int jt = t0; jt < t1; ++jt) {
+              const double4 pt = spt[jt];
+              double ct;
+              ++n_mt;
+              if (!doublet(M, rM, P3{pt.x, pt.y, pt.z}, pt.w, false, tan_dphi, ct)) continue;
+              ++n_cot;
+              if (!(fabs(cb - ct) <= tol)) continue;
+              ++n_tri;
+              try_triplet(B, b, M, pt, sorted[jt], rmin, best);
             }
           }
         }
@@ -484,6 +574,7 @@ __global__ void __launch_bounds__(64 * kTriWaves) k_sd_triplets(
     if (in_lds) {
       if (btail > bhead) run_bottoms();  // the last, partial batch
       if (ptail > phead) run_pairs();    // fewer than 64 left after run_bottoms
+      run_picked();
     }
     // 3. the middle's best KEEP over the lanes: KEEP rounds of a butterfly
     //    minimum over the lanes' next unused candidate ((B, T) pairs are
@@ -595,7 +686,7 @@ size_t seed_workspace_bytes(long long rows, long long n_sp, int n_events, int n_
   const long long nbins = seed_bin_count(n_events, n_layers) + 1;
   const long long nb = (n > nbins ? n : nbins) / scan_detail::kScanBlock + 2;
   return 5 * al256s((size_t)n * 4) + al256s((size_t)n * 8 * kKeep) + al256s((size_t)n * 32) +
-         3 * al256s((size_t)nbins * 4) + al256s((size_t)nb * 8) + 256 + 512;
+         3 * al256s((size_t)nbins * 4) + al256s((size_t)nb * 8) + 256 + kXcds * kLine * 4 + 512;
 }
 
 hipError_t launch_seed(const GeomDev& g, int n_events, int n_surfaces, const int* moff, long long n_sp,
@@ -632,27 +723,28 @@ hipError_t launch_seed(const GeomDev& g, int n_events, int n_surfaces, const int
   p += al256s((size_t)(nbins + 1) * 4);
   unsigned* rlim = reinterpret_cast<unsigned*>(p);
   p += 256;
+  int* queue = reinterpret_cast<int*>(p);
+  p += kXcds * kLine * 4;
   long long* sums = reinterpret_cast<long long*>(p);
   const auto blocks = [](long long m) { return dim3((unsigned)((m + kSdBlock - 1) / kSdBlock)); };
   unsigned long long* work = reinterpret_cast<unsigned long long*>(counters);
   if (work) hipLaunchKernelGGL(k_sd_clear, dim3(1), dim3(64), 0, st, work);
   const long long nfill = n > nbins ? n : nbins;
-  if (nfill > 0) {
-    hipLaunchKernelGGL(k_sd_fill, blocks(nfill), dim3(kSdBlock), 0, st, n, head, cnt, (int)nbins, rlim);
-    hipLaunchKernelGGL(k_sd_fill, blocks(nbins > 0 ? nbins : 1), dim3(kSdBlock), 0, st, 0ll, head, fill, (int)nbins,
-                       (unsigned*)nullptr);
-  }
+  if (nfill > 0)
+    hipLaunchKernelGGL(k_sd_fill, blocks(nfill + kXcds * kLine), dim3(kSdBlock), 0, st, n, head, cnt, fill, nbins, rlim,
+                       queue);
   if (rows > 0) hipLaunchKernelGGL(k_sd_heads, blocks(rows), dim3(kSdBlock), 0, st, rows, moff, n, head);
   device_scan<OpMax, true>(head, n, row, sums, nullptr, st);
   if (n > 0)
-    hipLaunchKernelGGL(k_sd_key, blocks(n), dim3(kSdBlock), 0, st, n, n_surfaces, g, sl, row, xyz, key, cnt, rlim);
+    hipLaunchKernelGGL(k_sd_key, blocks(n), dim3(kSdBlock), 0, st, n, n_events, n_surfaces, g, sl, row, xyz, key, cnt,
+                       rlim);
   device_scan<OpSum, false>(cnt, nbins, start, sums, nullptr, st);
   if (n > 0) {
     hipLaunchKernelGGL(k_sd_place, blocks(n), dim3(kSdBlock), 0, st, n, key, start, fill, xyz, sorted, spt, count);
     const double rmin = kPtMin / (kKappa64 * fabs(bz));
     const double tan_dphi = tan(0.12);
-    hipLaunchKernelGGL(k_sd_triplets, dim3(kTriGrid), dim3(64 * kTriWaves), 0, st, nbins, sl, key, start, cnt,
-                       sorted, spt, rlim, rmin, tan_dphi, g_top_cap.load(), count, best, work);
+    hipLaunchKernelGGL(k_sd_triplets, dim3(kTriGrid), dim3(64 * kTriWaves), 0, st, n_events, sl, key, start,
+                       cnt, sorted, spt, rlim, queue, rmin, tan_dphi, g_top_cap.load(), count, best, work);
   }
   device_scan<OpSum, false>(count, n, head, sums, n_seeds, st);  // head now holds the seed offsets
   if (n > 0)

@@ -275,3 +275,47 @@ def test_seed_hand_placed_degenerate_cases(ckf, det_dense):
     assert n == 0
     n, _ = run([pt(30, 3, 0.3), pt(70, 7, 0.45), pt(120, 12, 0.6)])
     assert n == 0
+
+
+@pytest.mark.parametrize("n, kind", [(1, "arc"), (16, "line"), (17, "arc"), (129, "line"), (300, "arc"), (300, "line")])
+def test_seed_cuts_at_their_edges(ckf, det_dense, n, kind):
+    """n middles (one run of them, a run and one more, many runs), whose
+    triplets lie at the edges of the cuts: circles of about the smallest
+    radius that pass the origin at about D0_MAX, and lines at about D0_MAX
+    from it with their points off by a few float32 steps (radii up to 1e9 mm
+    and beyond, or no circle at all).  The seeds are the oracle's, in its
+    order."""
+    import math
+    import torch
+    from oracle import seeding as OS
+    rng = np.random.default_rng(n)
+    g = det_dense.as_arrays()
+    S = det_dense.n_surfaces
+    mods = np.array([int(np.nonzero(g["layer"] == L)[0][0]) for L in LAYERS[:3]])
+    pts = np.zeros((3, n, 3), np.float32)
+    rmin = OS.r_min(2.0)
+    for i in range(n):
+        d0 = float(rng.choice([0.0, 0.5, 1 - 1e-6, 1.0, 1 + 1e-6, 1.01])) * float(rng.choice([-1.0, 1.0]))
+        turn = rng.uniform(-math.pi, math.pi) if kind == "arc" else float(rng.choice([0.0, 0.5 * math.pi, rng.uniform(-3, 3)]))
+        for k, r in enumerate((32.0, 72.0, 116.0)):
+            if kind == "arc":
+                R = rmin * float(rng.choice([1 - 1e-7, 1.0, 1 + 1e-7, 1.3])) if k == 0 else R
+                c = R + d0  # centre at distance c on the y axis; the point at distance r of the origin
+                cosa = (c * c + r * r - R * R) / (2 * c * r)
+                x, y = r * math.sqrt(1 - cosa * cosa), r * cosa
+            else:
+                x, y = math.sqrt(r * r - d0 * d0), d0
+                y = float(np.float32(y)) + int(rng.integers(-1, 2)) * float(np.spacing(np.float32(max(abs(y), 1e-3))))
+            pts[k, i] = [x * math.cos(turn) - y * math.sin(turn), x * math.sin(turn) + y * math.cos(turn), 0.3 * r + i % 7]
+    order = np.argsort(mods)
+    xyz = pts[order].reshape(-1, 3)
+    li = np.repeat(order, n)
+    off = np.zeros(S + 1, np.int32)
+    for s in mods:
+        off[s + 1:] += n
+    t = lambda a, dt: torch.as_tensor(np.ascontiguousarray(a), dtype=dt, device="cuda")
+    sd, m = ckf.seed(ckf.Geometry(g), 1, t(off, torch.int32), t(xyz, torch.float32), t(np.zeros((3 * n, 2)), torch.float32),
+                     LAYERS, 2.0)
+    ref = OS.triplets(xyz.astype(np.float64), li, 2.0)
+    _say(f"# {n} {kind}s at the cuts' edges: {m} seeds")
+    assert [(b, mid, top) for mid, b, top, _ in ref] == [tuple(int(v) for v in r) for r in sd["spacepoints"].cpu().numpy()]
