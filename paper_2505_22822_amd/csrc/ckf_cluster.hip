@@ -41,6 +41,11 @@ constexpr int kClBlock = 256;  // a cell per thread, mostly: a thread's walks ar
 constexpr int kChunk = 256;    // cells from one chunk's first module to the next chunk's
 constexpr int kCap = 1024;     // cells of a chunk held in LDS (more, with a very full module: in the workspace)
 constexpr int kTotBlock = 1024;
+// Up to here each workgroup of the write pass adds up the totals before it (at
+// most four loads per thread), which is cheaper than a launch to scan them:
+// one event (590 chunks) 33.4 -> 29.7 us.  The sums grow with the square of the
+// chunks: 18 000 chunks would read 650 MB, where the scan takes 8 us.
+constexpr int kSumChunks = 1024;
 
 // The workspace: per cell (and for chunks that do not fit in LDS), and per
 // chunk its first row and its clusters (later: the clusters before it).
@@ -335,8 +340,8 @@ __device__ void cl_irregular(const CellsIn& c, const GeomDev& g, const float* __
 // of 150 000 cells, by the longest of them: 20 KB of LDS and 64 registers let
 // eight workgroups share a CU.  In chunks of 512 cells with 512 threads the
 // 4.7M cells of 32 events take 151 us instead of 116, with 320 163 us, with
-// 128 threads per 256 cells 176 us.  The whole call: one event 55 -> 33 us, 32
-// events 304 -> 182 us against per-cell arrays passed on through memory by
+// 128 threads per 256 cells 176 us.  The whole call: one event 55 -> 30 us, 32
+// events 304 -> 181 us against per-cell arrays passed on through memory by
 // twelve kernels.
 __global__ void __launch_bounds__(kClBlock) k_cl_chunks(CellsIn c, GeomDev g, const float* __restrict__ pitch, ClWs ws,
                                                         long long chunks, ClOut o) {
@@ -406,13 +411,25 @@ __global__ void __launch_bounds__(kTotBlock) k_cl_totals(long long chunks, ClWs 
 }
 
 // The results at their place: measurements, offsets, the cells' clusters.
+// kSum: each workgroup adds up the clusters of the chunks before it by itself.
+template <bool kSum>
 __global__ void __launch_bounds__(kClBlock) k_cl_write(CellsIn c, GeomDev g, const float* __restrict__ pitch, ClWs ws,
                                                        long long chunks, ClOut o) {
   if (*ws.irregular) return;
   const int t = threadIdx.x, chunk = blockIdx.x;
   const bool last = chunk == (int)chunks - 1;
   const int r0 = ws.chunk_row[chunk], r1 = last ? c.n_events * c.n_surfaces : ws.chunk_row[chunk + 1];
-  const int base = ws.total[chunk], total = ws.total[chunk + 1] - base;
+  int base, total;
+  if constexpr (kSum) {
+    __shared__ int sh[kClBlock / 64];
+    int sum = 0;
+    for (int b = t; b < chunk; b += kClBlock) sum += ws.total[b];
+    block_scan<false>(sum, sh, base);
+    total = ws.total[chunk];
+  } else {
+    base = ws.total[chunk];
+    total = ws.total[chunk + 1] - base;
+  }
   const long long first = c.offsets[r0];
   const int n = (int)(c.offsets[r1] - first);
   for (int k = t; k < total; k += kClBlock) cl_store(c, g, pitch, o, (long long)base + k, ws.meas[first + k]);
@@ -475,8 +492,12 @@ hipError_t launch_cluster(const CellsIn& c, const GeomDev& g, const float* pitch
   if (n > 0) {
     const dim3 grid((unsigned)chunks), block(kClBlock);
     hipLaunchKernelGGL(k_cl_chunks, grid, block, 0, st, c, g, pitch, w, chunks, o);
-    hipLaunchKernelGGL(k_cl_totals, dim3(1), dim3(kTotBlock), 0, st, chunks, w);
-    hipLaunchKernelGGL(k_cl_write, grid, block, 0, st, c, g, pitch, w, chunks, o);
+    if (chunks <= kSumChunks) {
+      hipLaunchKernelGGL(k_cl_write<true>, grid, block, 0, st, c, g, pitch, w, chunks, o);
+    } else {
+      hipLaunchKernelGGL(k_cl_totals, dim3(1), dim3(kTotBlock), 0, st, chunks, w);
+      hipLaunchKernelGGL(k_cl_write<false>, grid, block, 0, st, c, g, pitch, w, chunks, o);
+    }
   } else {
     hipLaunchKernelGGL(k_cl_none, blocks(rows + 1), dim3(256), 0, st, rows, moff);
   }

@@ -214,6 +214,38 @@ def test_cluster_chunk_boundaries(ckf, det_dense, sizes):
     assert np.all(np.abs(got["loc"] - ref["loc"]) <= 4e-6)
 
 
+@pytest.mark.parametrize("n_cells", [256 * 1024 - 1, 256 * 1024, 256 * 1024 + 1, 256 * 1300])
+def test_cluster_many_chunks(ckf, det_dense, n_cells):
+    """Calls of up to 1024 chunks and of more: copies of one event (the last
+    one cut off) give that event's clusters, numbered on from event to
+    event."""
+    from synth.cells import Cells
+    S = det_dense.n_surfaces
+    n_grid, _ = cell_grid(det_dense)
+    pix = [s for s in range(S) if n_grid[s, 0] >= 300 and n_grid[s, 1] >= 300][:64]
+    rng = np.random.default_rng(5)
+    at = [np.sort(rng.choice(60 * 80, 128, replace=False)) for _ in pix]
+    counts = np.zeros(S, np.int64)
+    counts[pix] = 128
+    n1 = int(counts.sum())
+    E = -(-n_cells // n1)
+    one = [np.concatenate([a % 80 for a in at]), np.concatenate([a // 80 for a in at]), rng.uniform(0.2, 2.0, n1)]
+    c0, c1, q = [np.tile(v, E)[:n_cells] for v in one]
+    off = np.minimum(np.r_[0, np.cumsum(np.tile(counts, E))], n_cells).astype(np.int32)
+    cells = lambda e, o, a: Cells(e, S, o, a[0].astype(np.int32), a[1].astype(np.int32), a[2].astype(np.float32),
+                                  np.full(len(a[0]), -1, np.int64))
+    _, ref = _run(ckf, det_dense, cells(1, off[:S + 1], [v[:n1] for v in one]))
+    _, got = _run(ckf, det_dense, cells(E, off, [c0, c1, q]))
+    assert ref["status"] == 0 and got["status"] == 0
+    k = len(ref["loc"])
+    full = n_cells // n1
+    np.testing.assert_array_equal(got["cell_cluster"][:full * n1],
+                                  (ref["cell_cluster"][None] + k * np.arange(full)[:, None]).ravel())
+    np.testing.assert_array_equal(got["loc"][:full * k], np.tile(ref["loc"], (full, 1)))
+    np.testing.assert_array_equal(got["offsets"][:full * S], (ref["offsets"][None, :-1] + k * np.arange(full)[:, None]).ravel())
+    assert got["offsets"][-1] == len(got["loc"]) == got["cell_cluster"].max() + 1
+
+
 def test_cluster_skips_a_row_out_of_order(ckf, det_dense):
     """A row that is out of order is flagged and skipped; the rows around it
     are clustered as if it were empty."""
