@@ -534,8 +534,8 @@ ckf_status ckf_seed_set_top_cap(int32_t cap, int32_t* cap_max);
  * chi2 and ndf [cap_tracks]; measurement ids must lie in [0, n_meas).
  * keep [cap_tracks] (device) receives 1 kept, 0 removed, -1 for a track
  * whose offsets or ids are out of range (it takes no part).  The rounds run
- * on the device: max_rounds (1..1024) of them are launched, and once no bad
- * track is left the remaining ones return at once.  info (device int32[2],
+ * on the device: at most max_rounds (1..1024), ending when no bad track is
+ * left.  info (device int32[2],
  * or NULL) receives the rounds that removed tracks and 1 if no bad track is
  * left (0: max_rounds did not suffice and the result is a prefix of the
  * greedy; call again with a larger bound).  workspace: at least

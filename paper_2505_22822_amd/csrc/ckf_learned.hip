@@ -90,7 +90,7 @@ __global__ void __launch_bounds__(64) k_mlp_forward(ModelDev M, const float* __r
 // workgroups on 256 CUs, a chain of seven dependent products): with one wave
 // per block every product was a serial run over its tiles.  A tile's sum runs
 // over k in the same order whichever wave forms it, so the gradient's bits do
-// not depend on the split.  4096 rows: 52 -> 21 us (one wave -> eight).
+// not depend on the split.  4096 rows: 52 -> 14 us (one wave -> eight).
 
 constexpr int kGradWaves = 8;
 constexpr int kLd = 72;  // row stride of the 64-wide LDS matrices: 36 banks, so a column of 16 rows is spread over them
@@ -305,7 +305,7 @@ __global__ void __launch_bounds__(64 * kGradWaves) k_mlp_grad(const float* __res
 
 // grad[p] = sum over blocks in block order; loss = summed loss / n.  One wave
 // per workgroup, sixteen blocks' values requested at a time (the sum itself
-// stays in block order): 64 blocks 16 -> 5 us.
+// stays in block order): 64 blocks 16 -> 4 us.
 constexpr int kReduceBlock = 64;
 
 __global__ void __launch_bounds__(kReduceBlock) k_mlp_reduce(const float* __restrict__ partial, int n_blocks,

@@ -316,3 +316,26 @@ def test_trained_network_saves_listing_work(ckf, det_dense, trained):
     assert ct["proposals"] >= 0.1 * ct["mlp_rows"]
     # (seen: 13 % fewer, 806,568 against 927,099, with 27 % of the rows confident)
     assert ct["nav_modules"] < 0.95 * cp["nav_modules"]
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 1024, 1025, 4096])
+def test_mlp_grad_row_counts(ckf, n):
+    """Row counts at the edges of a workgroup's 64 rows and of the 16 partial
+    sums that are added at a time, against the oracle that rounds to bfloat16
+    where the kernels do.  A sum of another order may round to the next
+    bfloat16 value (2^-8), up to three times in a row: 1.2e-2."""
+    import torch
+    from oracle import learned as OL
+    rng = np.random.Generator(np.random.PCG64(n))
+    params = _rand_params(200 + n)
+    x = rng.normal(0, 1, (n, 7)).astype(np.float32)
+    lab = rng.integers(0, 32, n).astype(np.int32)
+    dev = lambda a: torch.as_tensor(a, device="cuda")
+    g, loss = ckf.mlp_grad(dev(params), dev(x), dev(lab))
+    ol, ob = OL.loss_and_grad(params.astype(np.float64), x.astype(np.float64), lab, bf16=True)
+    assert abs(float(loss.item()) - ol) <= 1.2e-2 * abs(ol)
+    G, B = OL.unpack_params(g.cpu().numpy().astype(np.float64)), OL.unpack_params(ob)
+    for k in G:
+        rel = float(np.linalg.norm(G[k] - B[k]) / max(np.linalg.norm(B[k]), 1e-30))
+        _say(f"# {n} rows, {k}: {rel:.2e}")
+        assert rel <= 1.2e-2, k
