@@ -39,11 +39,14 @@ namespace {
 
 constexpr int kClBlock = 256;  // a cell per thread, mostly: a thread's walks are serial
 constexpr int kChunk = 256;    // cells from one chunk's first module to the next chunk's
-constexpr int kCap = 1024;     // cells of a chunk held in LDS (more, with a very full module: in the workspace)
+constexpr int kCap = 1024;     // cells of a chunk held in LDS there
+constexpr int kBigBlock = 1024;  // chunks with a fuller module: more threads,
+constexpr int kBigCap = 7680;    // more LDS (beyond it, the workspace)
+constexpr int kBigGrid = 256;
 constexpr int kTotBlock = 1024;
 // Up to here each workgroup of the write pass adds up the totals before it (at
 // most four loads per thread), which is cheaper than a launch to scan them:
-// one event (590 chunks) 33.4 -> 29.7 us.  The sums grow with the square of the
+// one event (590 chunks) 33.4 -> 29.7 us (31.3 with k_cl_big).  The sums grow with the square of the
 // chunks: 18 000 chunks would read 650 MB, where the scan takes 8 us.
 constexpr int kSumChunks = 1024;
 
@@ -56,12 +59,13 @@ struct ClWs {
   float4* meas;              // [n_cells] measurement k of a chunk, at its first cell + k: loc0, loc1, row (as bits)
   int* chunk_row;            // [chunks]
   int* total;                // [chunks + 1]
-  int* irregular;
+  int* big;                  // [chunks] the chunks of more than kCap cells
+  int *n_big, *irregular;
 };
 
 __global__ void k_cl_clear(int* status, ClWs w) {
   *status = 0;
-  *w.irregular = 0;
+  *w.irregular = *w.n_big = 0;
 }
 
 // Offsets checked; the first row of each chunk: chunk b starts at the first
@@ -122,7 +126,7 @@ __device__ __forceinline__ void link_pair(int* parent, int i, int j) {
 
 // Inclusive scan of one value per thread over the workgroup (sum or max; max
 // of values >= -1); `last` is the scan's last value.
-template <bool kMax, int kThreads = kClBlock>
+template <bool kMax, int kThreads>
 __device__ __forceinline__ int block_scan(int v, int* sh, int& last) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
 #pragma unroll
@@ -174,14 +178,15 @@ __device__ __forceinline__ bool cl_link(const ClRun& R, int i) {
 
 // Forest and numbers of the n cells of R (positions loaded, modules' first
 // cells marked in start, the rest of start -1).  Returns the clusters.
+template <int kT>
 __device__ __forceinline__ int cl_number(const ClRun& R, int n, int* sh, int* status) {
   const int t = threadIdx.x;
   int carry = -1;
-  for (int i0 = 0; i0 < n; i0 += kClBlock) {  // every cell's module: a running maximum of the first cells
+  for (int i0 = 0; i0 < n; i0 += kT) {  // every cell's module: a running maximum of the first cells
     const int i = i0 + t;
     const bool head = i < n && R.start[i] < -1;
     int top;
-    const int a = max(carry, block_scan<true>(head ? i : -1, sh, top));
+    const int a = max(carry, block_scan<true, kT>(head ? i : -1, sh, top));
     if (i < n) {
       if (!head) R.start[i] = a;
       R.parent[i] = i;
@@ -190,15 +195,15 @@ __device__ __forceinline__ int cl_number(const ClRun& R, int n, int* sh, int* st
   }
   __syncthreads();
   bool unsorted = false;
-  for (int i = t; i < n; i += kClBlock) unsorted |= cl_link(R, i);
+  for (int i = t; i < n; i += kT) unsorted |= cl_link(R, i);
   if (unsorted) atomicOr(status, CKF_CLUSTER_UNSORTED);
   __syncthreads();
   int total = 0;
-  for (int i0 = 0; i0 < n; i0 += kClBlock) {
+  for (int i0 = 0; i0 < n; i0 += kT) {
     const int i = i0 + t;
     const bool root = i < n && cl_parent(R.parent, i) == i;
     int all;
-    const int k = total + block_scan<false>(root ? 1 : 0, sh, all) - 1;
+    const int k = total + block_scan<false, kT>(root ? 1 : 0, sh, all) - 1;
     if (root) {
       R.first[k] = i;
       R.parent[i] = -1 - k;
@@ -206,7 +211,7 @@ __device__ __forceinline__ int cl_number(const ClRun& R, int n, int* sh, int* st
     total += all;
   }
   __syncthreads();
-  for (int i = t; i < n; i += kClBlock) {  // up to a numbered cell (the root, or one on the way to it)
+  for (int i = t; i < n; i += kT) {  // up to a numbered cell (the root, or one on the way to it)
     int y = cl_parent(R.parent, i);
     if (y < 0) continue;
     while (y >= 0) y = cl_parent(R.parent, y);
@@ -276,6 +281,7 @@ __device__ __forceinline__ void cl_store(const CellsIn& c, const GeomDev& g, con
 // rows do not end at the last cell): one workgroup takes all cells, in the
 // workspace.  A cell belongs to the highest-numbered valid row that begins at
 // or before it, and rows out of order are skipped.
+template <int kT>
 __device__ void cl_irregular(const CellsIn& c, const GeomDev& g, const float* __restrict__ pitch, const ClWs& ws,
                              int* sh, const ClOut& o) {
   const int t = threadIdx.x;
@@ -283,23 +289,23 @@ __device__ void cl_irregular(const CellsIn& c, const GeomDev& g, const float* __
   const long long rows = (long long)c.n_events * c.n_surfaces;
   const ClRun R{ws.pos, ws.start, ws.parent, ws.first};
   int* mark = ws.first;  // (the highest row that begins at each cell, until the clusters are numbered)
-  for (int i = t; i < n; i += kClBlock) {
+  for (int i = t; i < n; i += kT) {
     R.start[i] = -1;
     mark[i] = -1;
     R.pos[i] = make_int2(c.c0[i], c.c1[i]);
   }
   __syncthreads();
-  for (long long r = t; r < rows; r += kClBlock) {
+  for (long long r = t; r < rows; r += kT) {
     const int a = c.offsets[r], b = c.offsets[r + 1];
     if (a >= 0 && b > a && (long long)b <= c.n_cells) atomicMax(&mark[a], (int)r);
   }
   __syncthreads();
   int carry = -1;
-  for (int i0 = 0; i0 < n; i0 += kClBlock) {  // a later row's first cell starts a module only if no higher row did
+  for (int i0 = 0; i0 < n; i0 += kT) {  // a later row's first cell starts a module only if no higher row did
     const int i = i0 + t;
     int top;
     const int m = i < n ? cl_parent(mark, i) : -1;
-    const int before = block_scan<true>(m, sh, top);
+    const int before = block_scan<true, kT>(m, sh, top);
     // (the running maximum at i exceeds the one before i exactly where a module starts)
     const int prev = __shfl_up(before, 1);
     if ((threadIdx.x & 63) == 63) sh[threadIdx.x >> 6] = before;
@@ -310,17 +316,17 @@ __device__ void cl_irregular(const CellsIn& c, const GeomDev& g, const float* __
     __syncthreads();
   }
   __syncthreads();
-  const int total = cl_number(R, n, sh, o.status);
-  for (int k = t; k < total; k += kClBlock) {
+  const int total = cl_number<kT>(R, n, sh, o.status);
+  for (int k = t; k < total; k += kT) {
     const int f = R.first[k], h = R.start[f];
     // (the first cell at least, should its row end before it)
     const int end = h == -1 ? 0 : min(n, max(c.offsets[-2 - R.start[h < 0 ? f : h] + 1], f + 1));
     cl_store(c, g, pitch, o, k, cl_measure(c, g, pitch, R, c.q, k, end));
   }
   if (o.cell_cluster)
-    for (int i = t; i < n; i += kClBlock) o.cell_cluster[i] = R.start[i] == -1 ? -1 : -1 - R.parent[i];
+    for (int i = t; i < n; i += kT) o.cell_cluster[i] = R.start[i] == -1 ? -1 : -1 - R.parent[i];
   // a row's first measurement: the clusters that begin before its first cell
-  for (long long r = t; r <= rows; r += kClBlock) {
+  for (long long r = t; r <= rows; r += kT) {
     const long long a = r < rows ? c.offsets[r] : c.n_cells;
     int k = total;
     if (a >= 0 && a < c.n_cells) {
@@ -335,48 +341,92 @@ __device__ void cl_irregular(const CellsIn& c, const GeomDev& g, const float* __
   }
 }
 
+// A chunk's cells loaded into R, clustered, numbered and measured.
+template <int kT>
+__device__ __forceinline__ void cl_chunk(const CellsIn& c, const GeomDev& g, const float* __restrict__ pitch,
+                                         const ClWs& ws, const ClRun& R, int chunk, int r0, int r1, long long first,
+                                         int n, int* sh, int* status) {
+  const int t = threadIdx.x;
+  for (int i = t; i < n; i += kT) {
+    R.pos[i] = make_int2(c.c0[first + i], c.c1[first + i]);
+    R.start[i] = -1;
+  }
+  __syncthreads();
+  for (int r = r0 + t; r < r1; r += kT) {
+    const int a = c.offsets[r];
+    if (c.offsets[r + 1] > a) R.start[a - first] = -2 - r;
+  }
+  __syncthreads();
+  const int total = cl_number<kT>(R, n, sh, status);
+  if (t == 0) ws.total[chunk] = total;
+  for (int k = t; k < total; k += kT) ws.meas[first + k] = cl_measure(c, g, pitch, R, c.q + first, k, n);
+  for (int i = t; i < n; i += kT) ws.num[first + i] = -1 - R.parent[i];
+}
+
+// A chunk's rows and cells.
+__device__ __forceinline__ void chunk_range(const CellsIn& c, const ClWs& ws, long long chunks, int chunk, int& r0,
+                                            int& r1, long long& first, int& n) {
+  r0 = ws.chunk_row[chunk];
+  r1 = chunk == (int)chunks - 1 ? c.n_events * c.n_surfaces : ws.chunk_row[chunk + 1];
+  first = c.offsets[r0];
+  n = (int)(c.offsets[r1] - first);
+}
+
 // Clusters, numbers and local positions of one chunk per workgroup.  Bound by
 // the serial walks of the cells (link and sums, LDS reads) and, for one event
 // of 150 000 cells, by the longest of them: 20 KB of LDS and 64 registers let
 // eight workgroups share a CU.  In chunks of 512 cells with 512 threads the
-// 4.7M cells of 32 events take 151 us instead of 116, with 320 163 us, with
-// 128 threads per 256 cells 176 us.  The whole call: one event 55 -> 30 us, 32
-// events 304 -> 181 us against per-cell arrays passed on through memory by
+// 4.7M cells of 32 events took 151 us instead of 116, with 320 163 us, with
+// 128 threads per 256 cells 176 us.  The whole call: one event 55 -> 31 us, 32
+// events 304 -> 172 us against per-cell arrays passed on through memory by
 // twelve kernels.
 __global__ void __launch_bounds__(kClBlock) k_cl_chunks(CellsIn c, GeomDev g, const float* __restrict__ pitch, ClWs ws,
-                                                        long long chunks, ClOut o) {
+                                                        long long chunks, int* __restrict__ status) {
   __shared__ int2 s_pos[kCap];
   __shared__ int s_start[kCap], s_parent[kCap], s_first[kCap];
   __shared__ int sh[kClBlock / 64];
-  if (*ws.irregular) {
-    if (blockIdx.x == 0) cl_irregular(c, g, pitch, ws, sh, o);
+  if (*ws.irregular) return;
+  int r0, r1, n;
+  long long first;
+  chunk_range(c, ws, chunks, blockIdx.x, r0, r1, first, n);
+  if (n > kCap) {
+    if (threadIdx.x == 0) ws.big[atomicAdd(ws.n_big, 1)] = blockIdx.x;
     return;
   }
-  const int t = threadIdx.x, chunk = blockIdx.x;
-  const int r0 = ws.chunk_row[chunk], r1 = chunk == (int)chunks - 1 ? c.n_events * c.n_surfaces : ws.chunk_row[chunk + 1];
-  const long long first = c.offsets[r0];
-  const int n = (int)(c.offsets[r1] - first);
-  const auto run = [&](const ClRun& R) {
-    for (int i = t; i < n; i += kClBlock) {
-      R.pos[i] = make_int2(c.c0[first + i], c.c1[first + i]);
-      R.start[i] = -1;
-    }
+  cl_chunk<kClBlock>(c, g, pitch, ws, ClRun{s_pos, s_start, s_parent, s_first}, blockIdx.x, r0, r1, first, n, sh,
+                     status);
+}
+
+// The chunks of more than kCap cells, and irregular calls.  Mostly there are
+// none: 3 us of an event's call, and the common kernel is the better for it
+// (without these paths in it, 32 events 116 -> 104 us).  300 modules of 2000
+// cells: the call 236 us with such chunks worked on in memory by 256 threads,
+// 119 here.  Beyond kBigCap (a pixel module 8 % full) a chunk is bound by its
+// workgroup's reads past the caches: 100 modules of 8000 cells take 590 us.
+__global__ void __launch_bounds__(kBigBlock) k_cl_big(CellsIn c, GeomDev g, const float* __restrict__ pitch, ClWs ws,
+                                                      long long chunks, ClOut o) {
+  __shared__ int2 s_pos[kBigCap];
+  __shared__ int s_start[kBigCap], s_parent[kBigCap], s_first[kBigCap];
+  __shared__ int sh[kBigBlock / 64];
+  if (*ws.irregular) {
+    if (blockIdx.x == 0) cl_irregular<kBigBlock>(c, g, pitch, ws, sh, o);
+    return;
+  }
+  const int n_big = *ws.n_big;
+  for (int i = blockIdx.x; i < n_big; i += gridDim.x) {
+    const int chunk = ws.big[i];
+    int r0, r1, n;
+    long long first;
+    chunk_range(c, ws, chunks, chunk, r0, r1, first, n);
+    if (n <= kBigCap)
+      cl_chunk<kBigBlock>(c, g, pitch, ws, ClRun{s_pos, s_start, s_parent, s_first}, chunk, r0, r1, first, n, sh,
+                          o.status);
+    else
+      cl_chunk<kBigBlock>(c, g, pitch, ws,
+                          ClRun{ws.pos + first, ws.start + first, ws.parent + first, ws.first + first}, chunk, r0, r1,
+                          first, n, sh, o.status);
     __syncthreads();
-    for (int r = r0 + t; r < r1; r += kClBlock) {
-      const int a = c.offsets[r];
-      if (c.offsets[r + 1] > a) R.start[a - first] = -2 - r;
-    }
-    __syncthreads();
-    const int total = cl_number(R, n, sh, o.status);
-    if (t == 0) ws.total[chunk] = total;
-    for (int k = t; k < total; k += kClBlock)
-      ws.meas[first + k] = cl_measure(c, g, pitch, R, c.q + first, k, n);
-    for (int i = t; i < n; i += kClBlock) ws.num[first + i] = -1 - R.parent[i];
-  };
-  if (n <= kCap)
-    run(ClRun{s_pos, s_start, s_parent, s_first});
-  else
-    run(ClRun{ws.pos + first, ws.start + first, ws.parent + first, ws.first + first});
+  }
 }
 
 // One workgroup: the chunks' clusters become the clusters before each chunk.
@@ -424,7 +474,7 @@ __global__ void __launch_bounds__(kClBlock) k_cl_write(CellsIn c, GeomDev g, con
     __shared__ int sh[kClBlock / 64];
     int sum = 0;
     for (int b = t; b < chunk; b += kClBlock) sum += ws.total[b];
-    block_scan<false>(sum, sh, base);
+    block_scan<false, kClBlock>(sum, sh, base);
     total = ws.total[chunk];
   } else {
     base = ws.total[chunk];
@@ -466,7 +516,9 @@ ClWs cl_view(void* ws, long long n, size_t* bytes) {
   for (int** q : {&w.start, &w.parent, &w.first, &w.num}) *q = reinterpret_cast<int*>(take(m * 4));
   w.chunk_row = reinterpret_cast<int*>(take(nc * 4));
   w.total = reinterpret_cast<int*>(take((nc + 4) * 4));
-  w.irregular = reinterpret_cast<int*>(take(4));
+  w.big = reinterpret_cast<int*>(take(nc * 4));
+  w.n_big = reinterpret_cast<int*>(take(8));
+  w.irregular = w.n_big + 1;
   if (bytes) *bytes = at;
   return w;
 }
@@ -491,7 +543,9 @@ hipError_t launch_cluster(const CellsIn& c, const GeomDev& g, const float* pitch
   hipLaunchKernelGGL(k_cl_rows, blocks(rows + 1), dim3(256), 0, st, c, w, chunks, status);
   if (n > 0) {
     const dim3 grid((unsigned)chunks), block(kClBlock);
-    hipLaunchKernelGGL(k_cl_chunks, grid, block, 0, st, c, g, pitch, w, chunks, o);
+    hipLaunchKernelGGL(k_cl_chunks, grid, block, 0, st, c, g, pitch, w, chunks, status);
+    hipLaunchKernelGGL(k_cl_big, dim3((unsigned)(chunks < kBigGrid ? chunks : kBigGrid)), dim3(kBigBlock), 0, st, c, g,
+                       pitch, w, chunks, o);
     if (chunks <= kSumChunks) {
       hipLaunchKernelGGL(k_cl_write<true>, grid, block, 0, st, c, g, pitch, w, chunks, o);
     } else {
