@@ -374,7 +374,7 @@ __device__ __forceinline__ void chunk_range(const CellsIn& c, const ClWs& ws, lo
 
 // Clusters, numbers and local positions of one chunk per workgroup.  Bound by
 // the serial walks of the cells (link and sums, LDS reads) and, for one event
-// of 150 000 cells, by the longest of them: 20 KB of LDS and 64 registers let
+// of 150 000 cells, by the longest of them: 20 KB of LDS and 32 registers let
 // eight workgroups share a CU.  In chunks of 512 cells with 512 threads the
 // 4.7M cells of 32 events took 151 us instead of 116, with 320 163 us, with
 // 128 threads per 256 cells 176 us.  The whole call: one event 55 -> 31 us, 32

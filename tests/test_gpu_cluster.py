@@ -214,6 +214,29 @@ def test_cluster_chunk_boundaries(ckf, det_dense, sizes):
     assert np.all(np.abs(got["loc"] - ref["loc"]) <= 4e-6)
 
 
+@pytest.mark.parametrize("n", [7680, 7681])
+def test_cluster_full_module(ckf, det_dense, n):
+    """One module with the most cells that a workgroup holds on chip, and one
+    more: every cell's cluster and the centroids are the oracle's."""
+    from oracle import clustering as OC
+    from synth.cells import Cells
+    S = det_dense.n_surfaces
+    n_grid, pitch = cell_grid(det_dense)
+    s = [k for k in range(S) if n_grid[k, 0] >= 300 and n_grid[k, 1] >= 300][1]
+    rng = np.random.default_rng(n)
+    at = np.sort(rng.choice(250 * 250, n, replace=False))
+    off = np.zeros(S + 1, np.int32)
+    off[s + 1:] = n
+    cells = Cells(1, S, off, (at % 250).astype(np.int32), (at // 250).astype(np.int32),
+                  rng.uniform(0.2, 2.0, n).astype(np.float32), np.full(n, -1, np.int64))
+    ref = OC.cluster(cells, det_dense.as_arrays(), pitch)
+    _, got = _run(ckf, det_dense, cells)
+    assert got["status"] == 0
+    np.testing.assert_array_equal(got["offsets"], ref["offsets"])
+    np.testing.assert_array_equal(got["cell_cluster"], ref["label"])
+    assert np.all(np.abs(got["loc"] - ref["loc"]) <= 6e-6)
+
+
 @pytest.mark.parametrize("n_cells", [256 * 1024 - 1, 256 * 1024, 256 * 1024 + 1, 256 * 1300])
 def test_cluster_many_chunks(ckf, det_dense, n_cells):
     """Calls of up to 1024 chunks and of more: copies of one event (the last
